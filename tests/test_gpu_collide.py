@@ -52,6 +52,57 @@ def test_collide_bit_exact(map_name, tile):
                 assert (got == exp).all(), (map_name, tile, n, dim, case)
 
 
+def _spheres_of(kind, n, dim, rng):
+    """Spheres that stress the filters of tiles 32 and up: scales, offsets,
+    outliers, radii and values that no box or 11-bit grid holds."""
+    S = np.zeros((n, 4), dtype=np.float32)
+    S[:, :3] = rng.random((n, 3), dtype=np.float32)
+    S[:, 3] = rng.random(n, dtype=np.float32) * np.float32(0.1 if dim == 3 else 0.01)
+    if kind == "tiny":          # squares underflow to zero or denormals
+        S *= np.float32(2.0 ** -74)
+    elif kind == "small":
+        S *= np.float32(2.0 ** -58)
+    elif kind == "huge":        # squares overflow
+        S *= np.float32(2.0 ** 64)
+    elif kind == "offset":      # a box far from the origin
+        S[:, :3] += np.float32(4096.0)
+    elif kind == "outliers":
+        S[rng.integers(0, n, max(1, n // 40)), :3] *= np.float32(1e6)
+    elif kind == "sorted":      # each row block's box is a small part of the space
+        S = S[np.argsort(S[:, 0], kind="stable")]
+    elif kind == "flat":        # one coordinate for all
+        S[:, :3] = np.float32(0.25)
+        S[::3, 3] = 0
+    elif kind == "big radii":   # a few spheres that overlap nearly all
+        S[rng.integers(0, n, max(1, n // 50)), 3] = np.float32(50.0)
+    elif kind == "negative":    # the sum of the radii is what is squared
+        S[::2, 3] *= -1
+    elif kind == "not finite":
+        for c in range(4):
+            k = rng.integers(0, n, (3, max(1, n // 60)))
+            S[k[0], c], S[k[1], c], S[k[2], c] = np.inf, np.nan, -np.inf
+    return S
+
+
+@pytest.mark.parametrize("kind", ["tiny", "small", "huge", "offset", "outliers", "sorted", "flat",
+                                  "big radii", "negative", "not finite"])
+@pytest.mark.parametrize("tile", [32, 64, 128])
+def test_collide_filters_miss_nothing(tile, kind):
+    import torch
+    tm = _tm()
+    # the smallest sizes that take the filters (3-D at tile 128: all), odd ones
+    sizes = {32: (6144, 6145), 64: (9217, 13313), 128: (2, 33, 130, 300, 1025, 13312)}[tile]
+    for n in sizes:
+        for dim in (1, 3):
+            S = _spheres_of(kind, n, dim, np.random.default_rng(n + dim))
+            exp = oracle.collide(S, dim)
+            for map_name in ("lambda", "bb", "rb"):
+                note("collide", kind, tile, map_name, n, dim)
+                counts = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+                tm.Plan(n, tile, map_name, include_diag=False).collide(dev(S), counts, dim=dim)
+                assert (host(counts) == exp).all(), (kind, tile, map_name, n, dim)
+
+
 def test_collide_errors():
     import torch
     tm = _tm()
