@@ -19,7 +19,6 @@
 // side n - 2 shifted: (a, b, c) = (k + 2, j + 1, i), as the strict triangle
 // is the non-strict one of side n - 1 shifted by one row.
 #include <new>
-#include <type_traits>
 
 #include "common.hpp"
 #include "maps.hpp"
@@ -184,82 +183,191 @@ __device__ __forceinline__ bool near3(f4 a, f4 b, float r2)
 
 // Tile (i, j, k) holds the points a = 2 + k rho + ta, b = 1 + j rho + tb and
 // c = i rho + tc (strict triples; the non-strict domain has no offsets).
-// The three neighbour relations between the tiles' points are formed once
-// as bit masks (one wave ballot gives 64 / rho rows), so a pair (a, b) of
-// neighbours finds all its triangles with one AND and a population count:
-// rho^2 distance tests per relation instead of rho^3 per triple.
-template <int TILE>
-struct TriShape {
-    static constexpr int NT = TILE == 8 ? 64 : 256;  // one wave holds the 64 pairs of rho = 8
-};
+//
+// A workgroup takes a strip of G consecutive blocks of the map (lambda: G
+// consecutive omega; BB: G grid columns of one grid row and layer).  i runs
+// fastest in both, so a strip falls into runs of tiles that share (j, k)
+// and cover one contiguous range of points c.  The neighbour relation a-b is
+// formed once per run, as a list of edges (one wave ballot gives 64 / rho
+// rows of rho pairs); only edges can be sides of a triangle, so the points
+// c are put to each edge and to no other pair:
+//  * up to 64 edges (the usual case: a few), one per lane of every wave: a
+//    wave takes 64 points c, one per lane, and reads the edges one by one
+//    through lane reads; b is looked at only when some c is near a.
+//  * more edges: the relations a-c and b-c of 64 points c as bit masks over
+//    the workgroup, and an AND and a population count per edge.
+// With the three relations of every tile formed anew (3 rho^2 distance tests
+// a tile, and a sweep over rho^2 pairs), n = 8192 under lambda took 1.50 ms at
+// tile 64 and 3.86 at tile 32; in this form 0.10 and 0.14.  What bounds it is
+// vector issue: 71 % of its cycles at 45 million wave instructions, about 16
+// per edge and 64 points c and 14 per ballot of the a-b relation.
+constexpr int kTriThreads = 256;
 
 template <int MAP, int TILE>
-__global__ void __launch_bounds__((TriShape<TILE>::NT)) k_triangles(TriArgs p, int32_t strict)
+__global__ void __launch_bounds__(kTriThreads) k_triangles(TriArgs p, int32_t strict, int32_t G,
+                                                           uint32_t strips)
 {
-    static_assert(TILE == 8 || TILE == 16 || TILE == 32 || TILE == 64, "mask width");
-    constexpr int NT = TriShape<TILE>::NT;
-    using M = typename std::conditional<TILE == 64, uint64_t, uint32_t>::type;  // a row of a relation
-    int32_t ti, tj, tk;
-    if (!tet_of_block<MAP>(p.g, ti, tj, tk)) return;
+    static_assert(TILE == 8 || TILE == 16 || TILE == 32 || TILE == 64, "rows per ballot");
+    constexpr int NW = kTriThreads / 64;  // waves
+    __shared__ f4 pts[2][TILE];              // 0: a (tile k), 1: b (tile j)
+    __shared__ uint16_t edges[TILE * TILE];  // 64 ta + tb
+    __shared__ int32_t hits[2][TILE];        // triangles of each a and b of the run
+    __shared__ uint64_t mask[2][TILE];       // relations a-c, b-c of 64 points c
+    __shared__ int32_t chits[64];
+    __shared__ int32_t ne;
+    __shared__ uint64_t sum[NW];
 
-    __shared__ f4 pts[3][TILE];          // 0: a (tile k), 1: b (tile j), 2: c (tile i)
-    __shared__ M mask[3][TILE];          // 0: a-b over b, 1: a-c over c, 2: b-c over c
+    const int t = threadIdx.x, l = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int32_t n = p.n;
-    const int32_t a0 = 2 * strict + tk * TILE, b0 = strict + tj * TILE, c0 = ti * TILE;
     const float nan = __builtin_nanf("");
-    const int t = threadIdx.x;
-    if (t < 3 * TILE) {
-        const int s = t / TILE, q = t % TILE;
-        const int32_t idx = (s == 0 ? a0 : (s == 1 ? b0 : c0)) + q;
-        pts[s][q] = idx < n ? p.p[idx] : f4{nan, nan, nan, nan};
-    }
-    __syncthreads();
+    const f4 none{nan, nan, nan, nan};
+    uint64_t found = 0;  // triangles this thread has counted
 
-    // masks: relation s pairs rows of set r(s) with columns of set c(s); a
-    // lane keeps its column point in registers through a relation's rows
-    constexpr int RPB = 64 / TILE;     // rows per ballot
-    constexpr int BPR = TILE / RPB;    // ballots per relation
-    constexpr int NW = NT / 64;        // waves
-    const int w = t >> 6, l = t & 63;
-    const int col = l % TILE;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        const int rs = s == 2 ? 1 : 0, cs = s == 0 ? 1 : 2;
-        const f4 pc = pts[cs][col];
-        for (int k = w; k < BPR; k += NW) {
-            const int row = k * RPB + l / TILE;
-            const bool hit = near3(pts[rs][row], pc, p.r2);
-            const uint64_t bal = __ballot(hit);
-            if (l % TILE == 0) {
-                if constexpr (TILE == 64)
-                    mask[s][row] = bal;
-                else
-                    mask[s][row] = (M)((bal >> (l - l % TILE)) & ((1ull << TILE) - 1ull));
+    // lambda: strips L, L + gridDim.x, ...; BB: one run
+    for (uint32_t L = blockIdx.x; MAP == MAP_BB || L < strips; L += gridDim.x) {
+        uint64_t g = 0, gend = 1;  // the strip's blocks [g, gend)
+        if constexpr (MAP == MAP_LAMBDA) {
+            g = (uint64_t)L * (uint32_t)G;
+            gend = g + (uint32_t)G < p.g.T ? g + (uint32_t)G : p.g.T;
+        }
+        while (g < gend) {
+            int32_t ti, tj, tk, len;
+            if constexpr (MAP == MAP_LAMBDA) {
+                if (p.g.flags & kLambda24) lambda3_tile_24((uint32_t)g, ti, tj, tk);
+                else lambda3_tile(g, p.g.flags, ti, tj, tk);
+                ti = __builtin_amdgcn_readfirstlane(ti);
+                tj = __builtin_amdgcn_readfirstlane(tj);
+                tk = __builtin_amdgcn_readfirstlane(tk);
+                len = tj - ti + 1 < (int32_t)(gend - g) ? tj - ti + 1 : (int32_t)(gend - g);
+            } else {
+                ti = (int32_t)blockIdx.x * G;
+                tj = (int32_t)blockIdx.y;
+                tk = (int32_t)blockIdx.z;
+                len = tj - ti + 1 < G ? tj - ti + 1 : G;
+                if (tj > tk || len < 1) return;
+            }
+            g += (uint32_t)(len > 0 ? len : 1);
+            // (no map can address points outside the domain)
+            if ((uint32_t)tk >= (uint32_t)p.g.m || (uint32_t)tj > (uint32_t)tk ||
+                (uint32_t)ti > (uint32_t)tj)
+                continue;
+            const int32_t a0 = 2 * strict + tk * TILE, b0 = strict + tj * TILE;
+
+            __syncthreads();  // the previous run is done with the LDS
+            if (t < 2 * TILE) {
+                const int32_t idx = t < TILE ? a0 + t : b0 + (t - TILE);
+                pts[t / TILE][t % TILE] = idx < n ? p.p[idx] : none;
+                hits[t / TILE][t % TILE] = 0;
+            }
+            if (t < 64) chits[t] = 0;
+            if (t == 0) ne = 0;
+            __syncthreads();
+
+            // the edges a-b with a > b
+            {
+                constexpr int RPB = 64 / TILE;  // rows per ballot
+                const int tb = l % TILE;
+                const f4 pb = pts[1][tb];
+                for (int q = w; q < TILE / RPB; q += NW) {
+                    const int ta = q * RPB + l / TILE;
+                    const bool hit = near3(pts[0][ta], pb, p.r2) && a0 + ta > b0 + tb;
+                    const uint64_t bal = __ballot(hit);
+                    if (bal == 0) continue;
+                    int32_t at = 0;
+                    if (l == 0) at = atomicAdd(&ne, (int32_t)__builtin_popcountll(bal));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                    if (hit) {
+                        const uint32_t before = __builtin_amdgcn_mbcnt_hi(
+                            (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+                        edges[at + before] = (uint16_t)(64 * ta + tb);
+                    }
+                }
+            }
+            __syncthreads();
+            const int E = __builtin_amdgcn_readfirstlane(ne);
+            if (E == 0) continue;
+
+            const int32_t c0 = ti * TILE, c1 = c0 + len * TILE < n ? c0 + len * TILE : n;
+            if (E <= 64) {
+                const int my = l < E ? edges[l] : 0;
+                const f4 ea = pts[0][my >> 6], eb = pts[1][my & 63];
+                const auto lane = [](float v, int e) {
+                    return __builtin_bit_cast(
+                        float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), e));
+                };
+                // long runs: the waves share the points c, short ones the edges
+                const bool share_c = c1 - c0 > 64 * (NW - 1);
+                const int32_t cstep = share_c ? 64 * NW : 64;
+                int32_t cb = share_c ? c0 + 64 * w : c0;
+                f4 pc = cb + l < c1 ? p.p[cb + l] : none;
+                for (; cb < c1; cb += cstep) {
+                    const f4 c = pc;
+                    const int32_t nc = cb + cstep + l;
+                    pc = nc < c1 ? p.p[nc] : none;  // in flight during the tests
+                    int32_t mine = 0;
+                    for (int e = share_c ? 0 : w; e < E; e += share_c ? 1 : NW) {
+                        const f4 a{lane(ea.x, e), lane(ea.y, e), lane(ea.z, e), 0.f};
+                        const bool na = near3(a, c, p.r2);
+                        if (!__any(na)) continue;
+                        const int id = __builtin_amdgcn_readlane(my, e);
+                        const f4 b{lane(eb.x, e), lane(eb.y, e), lane(eb.z, e), 0.f};
+                        const bool hit = na && near3(b, c, p.r2) && cb + l < b0 + (id & 63);
+                        const int k = __builtin_popcountll(__ballot(hit));
+                        if (k == 0) continue;
+                        mine += hit;
+                        if (l == 0) {
+                            found += (uint64_t)k;
+                            atomicAdd(&hits[0][id >> 6], k);
+                            atomicAdd(&hits[1][id & 63], k);
+                        }
+                    }
+                    if (mine) atomicAdd(&p.counts[cb + l], mine);
+                }
+            } else {
+                for (int32_t cb = c0; cb < c1; cb += 64) {
+                    const f4 c = cb + l < c1 ? p.p[cb + l] : none;
+                    for (int q = w; q < 2 * TILE; q += NW) {
+                        const uint64_t bal = __ballot(near3(pts[q / TILE][q % TILE], c, p.r2));
+                        if (l == 0) mask[q / TILE][q % TILE] = bal;
+                    }
+                    __syncthreads();
+                    for (int e = t; e < E; e += kTriThreads) {
+                        const int id = edges[e];
+                        uint64_t m = mask[0][id >> 6] & mask[1][id & 63];
+                        const int32_t below = b0 + (id & 63) - cb;  // points c < b
+                        if (below < 64) m &= below > 0 ? (1ull << below) - 1 : 0ull;
+                        if (!m) continue;
+                        const int k = __builtin_popcountll(m);
+                        found += (uint64_t)k;
+                        atomicAdd(&hits[0][id >> 6], k);
+                        atomicAdd(&hits[1][id & 63], k);
+                        for (; m; m &= m - 1) atomicAdd(&chits[__builtin_ctzll(m)], 1);
+                    }
+                    __syncthreads();
+                    if (t < 64 && chits[t]) {
+                        atomicAdd(&p.counts[cb + t], chits[t]);
+                        chits[t] = 0;
+                    }
+                }
+            }
+            __syncthreads();
+            if (t < 2 * TILE) {
+                const int32_t k = hits[t / TILE][t % TILE];
+                if (k) atomicAdd(&p.counts[t < TILE ? a0 + t : b0 + (t - TILE)], k);
             }
         }
+        if constexpr (MAP == MAP_BB) break;
     }
+    // one addition to the total per workgroup
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) found += __shfl_xor((unsigned long long)found, off, 64);
+    if (l == 0) sum[w] = found;
     __syncthreads();
-
-    // pairs (a, b): TILE^2 of them, over the NT threads
-    const bool same_kj = (tk == tj), same_ji = (tj == ti);
-    for (int q = t; q < TILE * TILE; q += NT) {
-        const int ta = q / TILE, tb = q % TILE;
-        // a > b: always across tiles, within one tile index iff ta >= tb
-        // (a = tb + 2 + ..., b = tb + 1 + ... on the shifted tetrahedron)
-        if (same_kj && ta < tb) continue;
-        if (!((mask[0][ta] >> tb) & 1u)) continue;
-        M m = mask[1][ta] & mask[2][tb];
-        if (same_ji) m &= (tb == TILE - 1) ? ~(M)0 : (((M)2 << tb) - 1);  // c <= b in the tile
-        if (!m) continue;
-        const int c = __builtin_popcountll((uint64_t)m);
-        atomicAdd(&p.counts[a0 + ta], c);
-        atomicAdd(&p.counts[b0 + tb], c);
-        atomicAdd(p.total, (unsigned long long)c);
-        while (m) {
-            const int tc = __builtin_ctzll((uint64_t)m);
-            m &= m - 1;
-            atomicAdd(&p.counts[c0 + tc], 1);
-        }
+    if (t == 0) {
+        uint64_t all = 0;
+        for (int q = 0; q < NW; ++q) all += sum[q];
+        if (all) atomicAdd(p.total, (unsigned long long)all);
     }
 }
 
@@ -271,16 +379,47 @@ __global__ void __launch_bounds__(256) k_tri_clear(int32_t *v, int64_t count,
     if (q == 0) *total = 0;
 }
 
+// Blocks per strip: up to 4096 points c, so that the edges of a run serve many
+// of them, while the strips stay more than the 2048 resident workgroups twice
+// over; strips of up to 512 points c need only cover the GPU's CUs twice,
+// since a run's fixed cost (its barriers and dependent loads) outweighs them.
+// Measured (us; blocks a strip): n = 8192, tile 64: 16 123, 32 108, 64 100;
+// tile 32: 32 197, 64 163, 128 139; n = 4000, tile 64: 8 47, 16 50, 32 57;
+// n = 2000, tile 64: 1 39, 2 35, 4 28, 8 25; n = 1000, tile 32: 1 30, 4 22, 8 17.
+static int32_t triangles_strip_len(const tri_tet *p)
+{
+    int32_t G = 4096 / p->tile;
+    while (G > 1 && p->T / (uint64_t)G < (G * p->tile > 512 ? 4096u : 512u)) G /= 2;
+    return G;
+}
+
+template <int MAP, int TILE>
+static void triangles_launch(const tri_tet *p, const TriArgs &a, hipStream_t s)
+{
+    const int32_t G = triangles_strip_len(p);
+    uint32_t strips = 0;
+    dim3 grid;
+    if (MAP == MAP_BB) {
+        grid = dim3((p->gx + G - 1) / G, p->gy, p->gz);
+    } else {
+        // (T < 2^32: the plan's grid)
+        strips = (uint32_t)((p->T + (uint32_t)G - 1) / (uint32_t)G);
+        // eight workgroups of four waves on each of 256 CUs; one workgroup
+        // per strip made 44,700 waves add to the one total: 297 us instead
+        // of 108 at n = 8192, tile 64
+        grid = dim3(strips < 2048u ? strips : 2048u);
+    }
+    k_triangles<MAP, TILE><<<grid, kTriThreads, 0, s>>>(a, p->strict, G, strips);
+}
+
 template <int MAP>
 static bool triangles_tile(const tri_tet *p, const TriArgs &a, hipStream_t s)
 {
-    const dim3 grid(p->gx, p->gy, p->gz);
-    const int32_t st = p->strict;
     switch (p->tile) {
-    case 8: k_triangles<MAP, 8><<<grid, TriShape<8>::NT, 0, s>>>(a, st); return true;
-    case 16: k_triangles<MAP, 16><<<grid, TriShape<16>::NT, 0, s>>>(a, st); return true;
-    case 32: k_triangles<MAP, 32><<<grid, TriShape<32>::NT, 0, s>>>(a, st); return true;
-    case 64: k_triangles<MAP, 64><<<grid, TriShape<64>::NT, 0, s>>>(a, st); return true;
+    case 8: triangles_launch<MAP, 8>(p, a, s); return true;
+    case 16: triangles_launch<MAP, 16>(p, a, s); return true;
+    case 32: triangles_launch<MAP, 32>(p, a, s); return true;
+    case 64: triangles_launch<MAP, 64>(p, a, s); return true;
     }
     return false;
 }

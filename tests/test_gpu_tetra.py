@@ -95,6 +95,29 @@ def test_triangles_bit_exact(map_name, tile):
 
 
 @pytest.mark.parametrize("map_name", ["bb", "lambda"])
+@pytest.mark.parametrize("tile", [8, 16, 32, 64])
+def test_triangles_dense_and_mixed(map_name, tile):
+    """Runs with every pair an edge, with none, and with up to and beyond 64
+    edges (the two ways a run's edges are put to its points c)."""
+    import torch
+    tm = _tm()
+    rng = np.random.default_rng(tile)
+    for n, spread in ((70, 0.01), (200, 0.3), (200, 0.6), (333, 0.02)):
+        P = np.zeros((n, 4), dtype=np.float32)
+        P[:, :3] = rng.random((n, 3), dtype=np.float32) * np.float32(spread)
+        P[n // 2:n // 2 + 40, 0] += np.float32(5.0)  # a block that sees only itself
+        P[3, 1] = np.nan
+        for rr in (np.float32(0.01), np.float32(0.0), np.float32(np.inf)):
+            exp_c, exp_t = oracle.triangles(P, rr)
+            note("triangles dense", map_name, tile, n, spread, rr)
+            counts = torch.full((n,), -5, dtype=torch.int32, device="cuda")
+            total = torch.full((1,), -5, dtype=torch.int64, device="cuda")
+            tm.TetPlan(n, tile, map_name, strict=True).triangles(dev(P), float(rr), counts, total)
+            assert (host(counts) == exp_c).all(), (map_name, tile, n, spread, rr)
+            assert int(host(total)[0]) == exp_t, (map_name, tile, n, spread, rr)
+
+
+@pytest.mark.parametrize("map_name", ["bb", "lambda"])
 @pytest.mark.parametrize("tile", [8, 16, 64])
 def test_tet_dummy_reaches_every_sum(map_name, tile):
     import torch
