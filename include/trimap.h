@@ -261,8 +261,10 @@ tri_status tri_tet_dummy(const tri_tet *plan, int32_t target, int32_t *sink, voi
  * the other way round: the result is in cur when steps is even, in nxt when
  * odd.  Requires ld % 4 == 0, ld >= n, 4-byte aligned pointers, steps >= 0.
  * With TRI_FLAG_LIFE_TEMPORAL in the plan (tiles 16, 32, 64; no graph) one
- * launch advances up to four generations from a tile staged with a 4-cell
- * halo (up to sixteen with a 16-cell halo for 64 x 64 tiles on grids of at
+ * launch advances several generations: under lambda at tile 64 (ld >= 16) up
+ * to 32 (50 up to n = 1536), in windows of the domain that the library tiles
+ * for the launch and lambda numbers; else up to four from a tile staged with
+ * a 4-cell halo (up to sixteen with a 16-cell halo for 64 x 64 tiles on grids of at
  * least 512 tiles whose ld is a multiple of 16 and whose buffers are
  * 16-byte aligned), the number of launches keeping the parity of `steps`.
  * Tile 64 with ld a multiple of 16 and 16-byte aligned buffers also runs

@@ -195,14 +195,8 @@ __device__ __forceinline__ uint32_t life_window_mask(int32_t gi, int32_t gj, int
 // staged window are not loaded; like cells beyond the byte-sliced window
 // they only reach the tile after more generations than the halo is deep.
 // ---------------------------------------------------------------------------
-// Generations per launch of the bit-sliced body with 16-byte rows in the
-// batched kernel (an 8-row, 8-cell halo: its 80 staged rows take the same
-// five 16-row rounds of loads as the 72 of a 4-row halo; a deeper halo does
-// not fit that kernel's 128 registers)
-constexpr int kLifeBitsMaxGen = 8;
-// The same in the stencil kernel: a 16-row, 16-cell halo (96 staged rows)
-// halves the launches, and so the round trips of the grid through HBM, for
-// a fifth more arithmetic per useful generation than the 8-row halo
+// Generations per launch of the bit-sliced bodies with 16-byte rows (a 16-row,
+// 16-cell halo)
 constexpr int kLifeBitsStencilGen = 16;
 
 template <int KH = kLifeMaxGen>

@@ -9,11 +9,13 @@
 // operation.  Cells outside the domain (j > i, outside the n x n square) are
 // zeroed as they are loaded and never stored, so the upper triangle is never
 // touched.
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
 #include "bodies.hpp"
 #include "common.hpp"
+#include "life_window.hpp"
 #include "maps.hpp"
 
 namespace trimap {
@@ -145,6 +147,89 @@ __global__ void __launch_bounds__(256) k_life_bits_strip_wide(LifeArgs p, int ge
     }
 }
 
+// ---------------------------------------------------------------------------
+// Temporal runs under lambda at tile 64: windows of many generations in
+// registers (life_window_body).  The domain is tiled anew for the launch, in
+// tiles of side h <= 2 cells less than the window's rows per generation,
+// G tiles of a tile row per window (w = G h cells), and workgroup s finds its
+// first tile through the row-aligned strip order and lambda.  The XCD
+// swizzle is always on: windows that share halo rows stay on one L2 (n =
+// 16384, 100 generations 378 -> 368 us, n = 3000 82 -> 72 us).
+//
+// Three windows (rows x cells; us per launch measured at n = 16384 for 1, 5, 9,
+// 13, 17, 25 generations, and n = 4096 for 1, 9, 25):
+//  * 256 x 256, four waves, four rows of two words per lane:
+//    72, 72, 75, 74, 77, 92; 10.5, 12.7, 19.1.  Many generations: the least
+//    halo for its registers (62, eight waves per SIMD).
+//  * 128 x 512, eight waves, two rows per lane: 60, 60, 64, 67, 100, 143;
+//    7.5, 10.9, 24.6.  Up to 8 generations, where a launch is bound by
+//    memory: a quad pair moves whole 128-byte lines, the others half lines.
+//  * 128 x 256, four waves, two rows per lane: up to n = 2560, where either
+//    other one would leave most CUs idle and a launch lasts as long as one
+//    window's chain of generations, about 0.27 us each with two rows per lane.
+// (288 x 512, twelve waves, three rows per lane: 66, 67, 69, 74, 75, 94; 10.8,
+// 14.9, 24.0.)
+//
+// 100 generations: n = 16384 820 -> 370 us (against 64 x 128 windows in LDS
+// with up to 16 generations a launch), n = 8192 298 -> 147, n = 4000 132 -> 74,
+// n = 2000 67 -> 59, n = 1000 (a pitch of 1000, which took the byte-sliced
+// kernel before) 219 -> 39.  25 generations a launch are bound by vector issue
+// (13.5 operations per word and generation), then by the 2 B per cell that
+// the launch moves, which overlap only in part: the windows that are
+// resident at once load, compute and store at about the same time.
+// ---------------------------------------------------------------------------
+template <int LX, int RR, int NW>
+__global__ void __launch_bounds__(64 * NW) k_life_window(LifeTile t, int gens, int32_t h, int32_t G,
+                                                         int32_t px)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t lds[LifeWindow<LX, RR, NW>::WORDS];
+    const uint32_t s = (uint32_t)xcd_swizzle(blockIdx.x, gridDim.x);
+    int32_t bi, bj;
+    lambda_tile_32(strip_align_first(s, (uint32_t)G), bi, bj);
+    bi = __builtin_amdgcn_readfirstlane(bi);
+    bj = __builtin_amdgcn_readfirstlane(bj);
+    life_window_body<LX, RR, NW>(t, bi * h, bj * h, h, G * h, px, gens,
+                                 __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lds);
+}
+
+template <int LX, int RR, int NW>
+static void life_window_launch_shape(const LifeTile &t, int gens, hipStream_t s)
+{
+    using S = LifeWindow<LX, RR, NW>;
+    // the largest G tiles of side h that the window yields after `gens`
+    // generations, with windows that start at multiples of 16 cells
+    const int px = (gens + 15) / 16 * 16;
+    int32_t G = 0, h = 0;
+    for (int32_t g = 1; g <= 4; ++g) {
+        const int32_t step = g == 4 ? 4 : (g == 2 ? 8 : 16);
+        const int32_t side = std::min(S::H - 2 * gens, (S::W - px - gens) / g) / step * step;
+        if ((int64_t)g * side * side > (int64_t)G * h * h) {
+            G = g;
+            h = side;
+        }
+    }
+    const uint32_t m = (uint32_t)((t.n + h - 1) / h);
+    const uint32_t windows = (uint32_t)strip_align_prefix(m, (uint32_t)G);
+    k_life_window<LX, RR, NW><<<windows, 64 * NW, 0, s>>>(t, gens, h, G, px);
+}
+
+// Generations per launch at most: 32 cells of halo leave 192 x 192 of 256 x
+// 256 cells, and cost as much as any halo above 16; on the smallest grids a
+// launch costs more than the cells that a 50-cell halo computes twice (n =
+// 1000, 100 generations: 4 launches of 25 50 us, 2 of 50 39 us; n = 2000 56, 62).
+static int life_window_gens(int64_t n) { return n <= 1536 ? 50 : 32; }
+
+// Grids the windows take: a pitch of at least one 16-cell chunk, and lane
+// offsets (up to 255 rows) below 2^32.
+static bool life_windows(const LifeTile &t) { return t.ld >= 16 && t.ld <= (1 << 24); }
+
+static void life_window_launch(const LifeTile &t, int gens, hipStream_t s)
+{
+    if (t.n <= 2560) life_window_launch_shape<4, 2, 4>(t, gens, s);
+    else if (gens <= 8) life_window_launch_shape<8, 2, 8>(t, gens, s);
+    else life_window_launch_shape<4, 4, 4>(t, gens, s);
+}
+
 // One generation of 64 x 64 tiles with the 1-cell halo of the paper's tiles,
 // bit-sliced, one wave per tile, 16-byte row moves
 template <int MAP>
@@ -220,12 +305,13 @@ static bool life_multi_kernel_tile(int tile, uint64_t tiles, bool vec, const voi
     case 16: fn = (const void *)k_life_multi<MAP, 16>; return true;
     case 32: fn = (const void *)k_life_multi<MAP, 32>; return true;
     case 64:
-        if (tiles >= (vec ? kLifeBitsMinTilesVec : kLifeBitsMinTiles)) {
-            fn = vec ? (const void *)k_life_bits<MAP, true> : (const void *)k_life_bits<MAP, false>;
-            threads = 64;
-            if (vec) maxgen = kLifeBitsStencilGen;
-        } else {
-            fn = (const void *)k_life_multi<MAP, 64>;
+        fn = (const void *)k_life_multi<MAP, 64>;
+        if constexpr (MAP != MAP_LAMBDA) {  // (lambda: windows, but for pitches below 16)
+            if (tiles >= (vec ? kLifeBitsMinTilesVec : kLifeBitsMinTiles)) {
+                fn = vec ? (const void *)k_life_bits<MAP, true> : (const void *)k_life_bits<MAP, false>;
+                threads = 64;
+                if (vec) maxgen = kLifeBitsStencilGen;
+            }
         }
         return true;
     }
@@ -235,11 +321,13 @@ static bool life_multi_kernel_tile(int tile, uint64_t tiles, bool vec, const voi
 template <int MAP>
 static const void *life_strip_kernel(int kh, bool wide)
 {
-    if (wide)
-        return kh == 1 ? (const void *)k_life_bits_strip_wide<MAP, 1>
-                       : (const void *)k_life_bits_strip_wide<MAP, kLifeBitsStencilGen>;
-    return kh == 1 ? (const void *)k_life_bits_strip<MAP, 1>
-                   : (const void *)k_life_bits_strip<MAP, kLifeBitsStencilGen>;
+    if (kh == 1)
+        return wide ? (const void *)k_life_bits_strip_wide<MAP, 1>
+                    : (const void *)k_life_bits_strip<MAP, 1>;
+    if constexpr (MAP != MAP_LAMBDA)  // (lambda's temporal runs take windows)
+        return wide ? (const void *)k_life_bits_strip_wide<MAP, kLifeBitsStencilGen>
+                    : (const void *)k_life_bits_strip<MAP, kLifeBitsStencilGen>;
+    return nullptr;
 }
 
 // the strip kernel of a plan (kh = 1: one generation; else the temporal one)
@@ -297,19 +385,12 @@ bool launch_life_multi_lambda(int tile, const TileGrid &g, const LifeTile &t, in
     case 16: k_life_multi<MAP_LAMBDA, 16><<<grid, 256, 0, s>>>(a, gens); return true;
     case 32: k_life_multi<MAP_LAMBDA, 32><<<grid, 256, 0, s>>>(a, gens); return true;
     case 64:
-        // the bit-sliced kernel with 16-byte rows: the shallower halo where
-        // it suffices (the batch's launches advance up to kLifeBitsMaxGen)
-        if (gens > kLifeMaxGen) {  // only the bit-sliced kernel with 16-byte rows goes beyond 4
-            if (!life_vec16(t)) return false;
-            if (gens <= kLifeBitsMaxGen)
-                k_life_bits<MAP_LAMBDA, true, kLifeBitsMaxGen><<<grid, 64, 0, s>>>(a, gens);
-            else
-                k_life_bits<MAP_LAMBDA, true><<<grid, 64, 0, s>>>(a, gens);
-        } else if (life_vec16(t) && g.T >= kLifeBitsMinTilesVec)
-            k_life_bits<MAP_LAMBDA, true, kLifeBitsMaxGen><<<grid, 64, 0, s>>>(a, gens);
-        else if (!life_vec16(t) && g.T >= kLifeBitsMinTiles)
-            k_life_bits<MAP_LAMBDA, false><<<grid, 64, 0, s>>>(a, gens);
-        else k_life_multi<MAP_LAMBDA, 64><<<grid, 256, 0, s>>>(a, gens);
+        if (life_windows(t)) {
+            life_window_launch(t, gens, s);
+        } else {
+            if (gens > kLifeMaxGen) return false;
+            k_life_multi<MAP_LAMBDA, 64><<<grid, 256, 0, s>>>(a, gens);
+        }
         return true;
     }
     return false;
@@ -459,13 +540,24 @@ extern "C" tri_status tri_launch_stencil(const tri_plan *p, uint8_t *cur, uint8_
     if (p->flags & TRI_FLAG_LIFE_TEMPORAL) {
         if (use_graph)
             return fail(TRI_E_UNSUPPORTED, "tri_launch_stencil: graphs of the temporal kernel are not built");
+        const bool windows = p->map == TRI_MAP_LAMBDA && p->tile == 64 && life_windows(a.t);
+        if (windows) {
+            const std::vector<int> sched = life_multi_schedule(steps, life_window_gens(p->n));
+            for (size_t k = 0; k < sched.size(); ++k) {
+                a.t.cur = (k & 1) ? nxt : cur;
+                a.t.nxt = (k & 1) ? cur : nxt;
+                life_window_launch(a.t, sched[k], s);
+                TRI_HIP(hipGetLastError());
+            }
+            return TRI_OK;
+        }
         const void *fn = nullptr;
         int threads = 256, maxgen = kLifeMaxGen;
         if (!life_multi_kernel(p, life_vec16(a.t), fn, threads, maxgen))
             return fail(TRI_E_UNSUPPORTED, "tri_launch_stencil: temporal blocking needs tile 16, 32 or 64");
         dim3 grid(p->gx, p->gy);
         StripGrid sg{};
-        const bool strips = life_strips(p, a.t);
+        const bool strips = p->map != TRI_MAP_LAMBDA && life_strips(p, a.t);
         if (strips) {
             fn = life_strip_fn(p, kLifeBitsStencilGen);
             threads = 256;

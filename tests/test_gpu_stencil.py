@@ -62,6 +62,37 @@ def test_life_bit_exact(map_name, tile, multiple):
             assert (got[:, :n][low] == exp[low]).all(), (map_name, tile, n, steps)
 
 
+@pytest.mark.parametrize("n", [13, 16, 17, 63, 64, 191, 192, 193, 257, 449, 1000, 1537, 2561, 2817])
+def test_life_windows_bit_exact(n):
+    """Temporal runs under lambda at tile 64: grids around the windows' sides
+    and around the sizes where the window (2560) and the generations per
+    launch (1536) change, generations per launch from 1 to 50, pitches that
+    are and are not multiples of 16, buffers that are and are not 16-byte
+    aligned.  (2561 and 2817 take the third window at 3 generations.)"""
+    import torch
+    tm = _tm()
+    low = np.tril(np.ones((n, n), dtype=bool))
+    p = tm.Plan(n, 64, "lambda", flags=tm.FLAG_LIFE_TEMPORAL)
+    for ld, shift in ((padded_ld(n, 4), 4), (padded_ld(n, 16) + 4, 0), (padded_ld(n, 16), 0)):
+        g = inputs.life(n, 0.3, seed=n + ld, ld=ld)
+        up = np.triu(np.ones((n, ld), dtype=bool), 1)
+        for steps in (1, 2, 16, 17, 50) if n < 1537 else (3, 9, 33):
+            note("life windows", n, ld, shift, steps)
+            bufs = []
+            for fill in (g, np.zeros_like(g)):
+                host_buf = fill.copy()
+                host_buf[up] = np.random.default_rng(steps).integers(0, 256, up.sum(), dtype=np.uint8)
+                raw = torch.full((n * ld + 64,), 9, dtype=torch.uint8, device="cuda")
+                raw[shift:shift + n * ld] = dev(host_buf).reshape(-1)
+                bufs.append((raw, raw[shift:shift + n * ld].view(n, ld), host_buf))
+            p.stencil(bufs[0][1], bufs[1][1], steps, ld=ld)
+            raw, res, start = bufs[steps % 2]
+            got, exp = host(res), oracle.gol(g, n, steps)
+            assert (got[:, :n][low] == exp[:, :n][low]).all(), (n, ld, shift, steps)
+            assert (got[up] == start[up]).all(), "cells above the diagonal written"
+            assert (host(raw)[:shift] == 9).all() and (host(raw)[shift + n * ld:] == 9).all()
+
+
 def test_life_long_run_and_composition():
     tm = _tm()
     n = 300
