@@ -11,6 +11,42 @@
 namespace trimap {
 
 // ---------------------------------------------------------------------------
+// Correctly rounded square root in five operations for x in [2^-96, 2^96]:
+// one Newton step from x rsq(x).  It equals the correctly rounded root for
+// every binary32 value of that range (all of them compared on the device);
+// __builtin_sqrtf, right for every x, takes about sixteen.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ float sqrt_near1(float x)
+{
+    const float y = __builtin_amdgcn_rsqf(x);
+    const float s = x * y, h = 0.5f * y;
+    return __builtin_fmaf(__builtin_fmaf(-s, s, x), h, s);
+}
+
+// The square roots of a lane's values v (all of them added first): the short
+// form when every active lane's values are in its range (a NaN gives NaN in
+// both forms).
+struct SqrtRange {
+    float lo = 0x1p96f, hi = 0x1p-96f;
+    __device__ __forceinline__ void add(float x)
+    {
+        lo = fminf(lo, x);
+        hi = fmaxf(hi, x);
+    }
+    template <int N>
+    __device__ __forceinline__ void roots(float (&v)[N]) const
+    {
+        if (__all(lo >= 0x1p-96f && hi <= 0x1p96f)) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = sqrt_near1(v[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = __builtin_sqrtf(v[k]);
+        }
+    }
+};
+
+// ---------------------------------------------------------------------------
 // Game of Life B3/S23 on the lower triangle (cells j > i and outside the
 // n x n square are dead and never written).  The tile plus a one-cell halo is
 // staged in LDS as 32-bit words of four cells; each thread updates a vertical

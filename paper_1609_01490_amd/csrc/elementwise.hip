@@ -11,17 +11,29 @@
 //    from global memory (they stay in L1/L2), nothing is staged in LDS.
 //
 // All are HBM-bound: 12 B (axpyt) or 4 B (xormul, edm4) of algorithmic
-// traffic per cell.  Rows move as 16-byte vectors; stores are non-temporal (the output
-// is not re-read).  UTM (thread space) has no tile and gets its own scalar
+// traffic per cell.  Rows move as 16-byte vectors where the pitch and the
+// matrices allow it.  How they are moved depends on where rows start:
+//  * every row on a 128-byte line (ld % 32 == 0, aligned matrices):
+//    non-temporal loads and stores (nothing is read twice).
+//  * else, axpyt, and tiles below 32: a tile's rows begin and end inside
+//    lines that the neighbouring tiles share.  Cached loads and stores, and
+//    under lambda the swizzled order, which keeps neighbours on one L2,
+//    where the halves of a line meet: n = 20001 (ld 20001), tile 32 1152 ->
+//    530 us, 64 823 -> 511, 128 662 -> 522; n = 8001, tile 64 137 -> 83.
+//  * else, xormul and edm4 at tiles from 32: k_lines, whose tiles are shifted,
+//    row by row, onto the lines.
+// UTM (thread space) has no tile and gets its own scalar
 // kernel, reading Y[j][i] straight from memory as the map implies.
 #include <type_traits>
 
+#include "bodies.hpp"
 #include "common.hpp"
 #include "maps.hpp"
 
 namespace trimap {
 
 TileGrid plan_tile_grid(const tri_plan *p);
+TileGrid plan_tile_grid_swizzled(const tri_plan *p);
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef int i4 __attribute__((ext_vector_type(4)));
@@ -35,6 +47,21 @@ struct ElemArgs {
     void *c;
     float a;
 };
+
+// Loads and stores of the output, non-temporal or cached.
+template <bool NT, typename V>
+__device__ __forceinline__ V load_as(const V *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+template <bool NT, typename V>
+__device__ __forceinline__ void store_as(V v, V *p)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
 
 // threads per workgroup and elements per vector for a tile size
 template <int TILE, bool VECTOR>
@@ -51,7 +78,7 @@ struct ElemShape {
     static_assert(RPP * PASSES == TILE, "tile shape");
 };
 
-template <int MAP, int TILE, bool VECTOR>
+template <int MAP, int TILE, bool VECTOR, bool STREAM>
 __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_axpyt(ElemArgs p)
 {
     using S = ElemShape<TILE, VECTOR>;
@@ -88,7 +115,7 @@ __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_axpyt(ElemArg
             i = i < n ? i : n - 1;
             jc = jc < cmax ? jc : cmax;
         }
-        xv[ps] = __builtin_nontemporal_load((const V *)(X + (int64_t)i * ld + jc));
+        xv[ps] = load_as<STREAM>((const V *)(X + (int64_t)i * ld + jc));
     }
 #pragma unroll
     for (int ps = 0; ps < S::PASSES; ++ps) {
@@ -98,7 +125,7 @@ __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_axpyt(ElemArg
             jr = jr < n ? jr : n - 1;
             ic = ic < cmax ? ic : cmax;
         }
-        yv[ps] = __builtin_nontemporal_load((const V *)(Y + (int64_t)jr * ld + ic));
+        yv[ps] = load_as<STREAM>((const V *)(Y + (int64_t)jr * ld + ic));
     }
 #pragma unroll
     for (int ps = 0; ps < S::PASSES; ++ps) {
@@ -128,14 +155,14 @@ __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_axpyt(ElemArg
             o.z = __fadd_rn(__fmul_rn(a, x4.z), ys[tc + 2][r]);
             o.w = __fadd_rn(__fmul_rn(a, x4.w), ys[tc + 3][r]);
             if (full || jc + 3 <= i) {
-                __builtin_nontemporal_store(o, (f4 *)crow);
+                store_as<STREAM>(o, (f4 *)crow);
             } else {  // the vector straddles the diagonal
                 crow[0] = o.x;
                 if (jc + 1 <= i) crow[1] = o.y;
                 if (jc + 2 <= i) crow[2] = o.z;
             }
         } else {
-            __builtin_nontemporal_store(__fadd_rn(__fmul_rn(a, xv[ps]), ys[tc][r]), crow);
+            store_as<STREAM>(__fadd_rn(__fmul_rn(a, xv[ps]), ys[tc][r]), crow);
         }
     }
 }
@@ -497,7 +524,7 @@ __global__ void __launch_bounds__(256) k_axpyt_strip_quads(ElemArgs p, StripGrid
     }
 }
 
-template <int MAP, int TILE, bool VECTOR>
+template <int MAP, int TILE, bool VECTOR, bool STREAM>
 __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_xormul(ElemArgs p)
 {
     using S = ElemShape<TILE, VECTOR>;
@@ -537,7 +564,7 @@ __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_xormul(ElemAr
             o.z = (int32_t)((ai ^ b2) + ui * (uint32_t)(jc + 2));
             o.w = (int32_t)((ai ^ b3) + ui * (uint32_t)(jc + 3));
             if (full || jc + 3 <= i) {
-                __builtin_nontemporal_store(o, (i4 *)crow);
+                store_as<STREAM>(o, (i4 *)crow);
             } else {
                 crow[0] = o.x;
                 if (jc + 1 <= i) crow[1] = o.y;
@@ -545,25 +572,30 @@ __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_xormul(ElemAr
             }
         } else {
             const uint32_t v = (ai ^ B[jc]) + (uint32_t)i * (uint32_t)jc;
-            __builtin_nontemporal_store((int32_t)v, crow);
+            store_as<STREAM>((int32_t)v, crow);
         }
     }
 }
 
-// |P_i - P_j| with a fixed operation order: differences, squares, the sum
-// ((dx^2 + dy^2) + dz^2) + dw^2, each rounded to binary32, then a correctly
-// rounded square root.
-__device__ __forceinline__ float dist4(f4 a, f4 b)
+// |P_i - P_j|^2 with a fixed operation order: differences, squares, the sum
+// ((dx^2 + dy^2) + dz^2) + dw^2, each rounded to binary32.  The distance is
+// its correctly rounded square root.
+__device__ __forceinline__ float square4(f4 a, f4 b)
 {
     const float dx = __fsub_rn(a.x, b.x), dy = __fsub_rn(a.y, b.y);
     const float dz = __fsub_rn(a.z, b.z), dw = __fsub_rn(a.w, b.w);
     float s = __fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy));
     s = __fadd_rn(s, __fmul_rn(dz, dz));
     s = __fadd_rn(s, __fmul_rn(dw, dw));
-    return __builtin_sqrtf(s);
+    return s;
 }
 
-template <int MAP, int TILE, bool VECTOR>
+// SHORT: the short square root, a few rows at a time (n = 4096, tile 64 12.0 ->
+// 10.0 us, n = 8192 35 -> 29).  Where the output is far larger than the caches
+// the launch is bound by its stores, and the long one, row by row, spreads
+// them better (n = 24000, tile 128 210 us, 222 with the short one; n = 32768
+// 384, 412; tile 64 402, 415).
+template <int MAP, int TILE, bool VECTOR, bool STREAM, bool SHORT>
 __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_edm4(ElemArgs p)
 {
     using S = ElemShape<TILE, VECTOR>;
@@ -586,30 +618,132 @@ __global__ void __launch_bounds__((ElemShape<TILE, VECTOR>::NT)) k_edm4(ElemArgs
 #pragma unroll
     for (int v = 0; v < S::VEC; ++v) pj[v] = P[jc + v < n ? jc + v : n - 1];
 
-#pragma unroll
-    for (int ps = 0; ps < S::PASSES; ++ps) {
-        const int r = tr + ps * S::RPP;
-        const int32_t i = i0 + r;
-        if (!full && (i >= n || jc > i)) continue;
-        const f4 pi = P[i];
+    // (VEC values of row i, from column jc)
+    const auto put = [&](int32_t i, const float *w) {
         float *crow = C + (int64_t)i * ld + jc;
         if constexpr (S::VEC == 4) {
-            f4 o;
-            o.x = dist4(pi, pj[0]);
-            o.y = dist4(pi, pj[1]);
-            o.z = dist4(pi, pj[2]);
-            o.w = dist4(pi, pj[3]);
             if (full || jc + 3 <= i) {
-                __builtin_nontemporal_store(o, (f4 *)crow);
+                store_as<STREAM>(f4{w[0], w[1], w[2], w[3]}, (f4 *)crow);
             } else {  // the vector straddles the diagonal
-                crow[0] = o.x;
-                if (jc + 1 <= i) crow[1] = o.y;
-                if (jc + 2 <= i) crow[2] = o.z;
+                crow[0] = w[0];
+                if (jc + 1 <= i) crow[1] = w[1];
+                if (jc + 2 <= i) crow[2] = w[2];
             }
         } else {
-            __builtin_nontemporal_store(dist4(pi, pj[0]), crow);
+            store_as<STREAM>(w[0], crow);
+        }
+    };
+    if constexpr (!SHORT) {
+#pragma unroll
+        for (int ps = 0; ps < S::PASSES; ++ps) {
+            const int32_t i = i0 + tr + ps * S::RPP;
+            if (!full && (i >= n || jc > i)) continue;
+            const f4 pi = P[i];
+            float o[S::VEC];
+#pragma unroll
+            for (int v = 0; v < S::VEC; ++v) o[v] = __builtin_sqrtf(square4(pi, pj[v]));
+            put(i, o);
+        }
+        return;
+    }
+    constexpr int PG = S::PASSES < 4 ? S::PASSES : 4;
+#pragma unroll
+    for (int p0 = 0; p0 < S::PASSES; p0 += PG) {
+        float o[PG * S::VEC];
+        SqrtRange range;
+#pragma unroll
+        for (int q = 0; q < PG; ++q) {
+            const int32_t i = i0 + tr + (p0 + q) * S::RPP;
+            const f4 pi = P[full || i < n ? i : n - 1];
+#pragma unroll
+            for (int v = 0; v < S::VEC; ++v) {
+                o[S::VEC * q + v] = square4(pi, pj[v]);
+                range.add(o[S::VEC * q + v]);
+            }
+        }
+        range.roots(o);
+#pragma unroll
+        for (int q = 0; q < PG; ++q) {
+            const int32_t i = i0 + tr + (p0 + q) * S::RPP;
+            if (!full && (i >= n || jc > i)) continue;
+            put(i, &o[S::VEC * q]);
         }
     }
+}
+
+// xormul and edm4 where rows do not start on 128-byte lines.  Row i's tiles
+// are shifted left by the row's misalignment s_i (in floats, 0 .. 31): tile
+// (bi, bj) takes the columns bj rho - s_i .. bj rho - s_i + rho - 1 of row i, a
+// whole number of lines, and the diagonal tile one line more, up to column
+// i.  So every store instruction writes two whole lines (one per half-wave,
+// two rows), whatever the pitch and the alignment.  The tile's column
+// operands, 32 more to the left and right, come from LDS.
+// n = 10007, ld 10007, tile 64, lambda: edm4 109 -> 43 us; n = 20001 440 -> 155 (tile 128 363 -> 164);
+// xormul n = 8001, tile 32 104 -> 29, tile 64 69 -> 28.
+template <int OP, int MAP, int TILE>
+__global__ void __launch_bounds__(8 * TILE) k_lines(ElemArgs p)
+{
+    using V = typename std::conditional<OP == TRI_OP_EDM4_F32, f4, uint32_t>::type;
+    using R = typename std::conditional<OP == TRI_OP_EDM4_F32, float, int32_t>::type;
+    constexpr int NT = 8 * TILE, NL = TILE / 32;  // threads, lines per tile row
+    constexpr int RP = 4;                          // rows per half-wave
+    int32_t bi, bj;
+    if (!tile_of_block<MAP>(p.g, bi, bj)) return;
+
+    __shared__ V rows[TILE], cols[TILE + 64];  // cols: columns j0 - 32 .. j0 + TILE + 31
+    const int32_t n = p.n;
+    const int64_t ld = p.ld;
+    const int32_t i0 = bi * TILE, j0 = bj * TILE;
+    const V *A = (const V *)p.x;
+    const V *B = OP == TRI_OP_EDM4_F32 ? A : (const V *)p.y;
+    for (int t = threadIdx.x; t < 2 * TILE + 64; t += NT) {
+        int32_t k = t < TILE ? i0 + t : j0 - 32 + (t - TILE);
+        k = k < 0 ? 0 : (k < n ? k : n - 1);
+        if (t < TILE) rows[t] = A[k];
+        else cols[t - TILE] = B[k];
+    }
+    __syncthreads();
+
+    const int hw = threadIdx.x >> 5, lane = threadIdx.x & 31;
+    const bool full = bj < bi && bj > 0 && i0 + TILE <= n;  // every cell is in the domain
+    // lines k0 .. k0 + NL - 1 of the half-wave's rows hw, hw + TILE / 4, ..
+    const auto pass = [&](auto lines, int k0) {
+        constexpr int K = lines;
+        R v[RP * K];
+        SqrtRange range;
+#pragma unroll
+        for (int u = 0; u < RP; ++u) {
+            const int r = hw + u * (TILE / RP);
+            const int32_t i = i0 + r;
+            const int32_t s = (int32_t)(((uintptr_t)((R *)p.c + (int64_t)i * ld) >> 2) & 31);
+            const V a = rows[r];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int t = 32 * (k0 + k) + lane - s;
+                const V b = cols[t + 32];
+                if constexpr (OP == TRI_OP_EDM4_F32) {
+                    v[K * u + k] = square4(a, b);
+                    range.add(v[K * u + k]);
+                } else {
+                    v[K * u + k] = (R)((a ^ b) + (uint32_t)i * (uint32_t)(j0 + t));
+                }
+            }
+        }
+        if constexpr (OP == TRI_OP_EDM4_F32) range.roots(v);
+#pragma unroll
+        for (int u = 0; u < RP; ++u) {
+            const int32_t i = i0 + hw + u * (TILE / RP);
+            R *const row = (R *)p.c + (int64_t)i * ld;
+            const int32_t s = (int32_t)(((uintptr_t)row >> 2) & 31);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int32_t j = j0 + 32 * (k0 + k) + lane - s;
+                if (full || (i < n && j >= 0 && j <= i)) __builtin_nontemporal_store(v[K * u + k], row + j);
+            }
+        }
+    };
+    pass(std::integral_constant<int, NL>{}, 0);
+    if (bi == bj) pass(std::integral_constant<int, 1>{}, NL);
 }
 
 // UTM: thread k owns cell utm_cell(k); no tile, no LDS.
@@ -629,7 +763,7 @@ __global__ void __launch_bounds__(kUtmThreads) k_elem_utm(ElemArgs p, int64_t el
             __fadd_rn(__fmul_rn(p.a, X[(int64_t)i * ld + j]), Y[(int64_t)j * ld + i]);
     } else if constexpr (OP == TRI_OP_EDM4_F32) {
         const f4 *P = (const f4 *)p.x;
-        ((float *)p.c)[(int64_t)i * ld + j] = dist4(P[i], P[j]);
+        ((float *)p.c)[(int64_t)i * ld + j] = __builtin_sqrtf(square4(P[i], P[j]));
     } else {
         const uint32_t *A = (const uint32_t *)p.x;
         const uint32_t *B = (const uint32_t *)p.y;
@@ -638,28 +772,47 @@ __global__ void __launch_bounds__(kUtmThreads) k_elem_utm(ElemArgs p, int64_t el
     }
 }
 
-template <int OP, int MAP, int TILE, bool VECTOR>
+// How a launch moves rows (see the head of this file).
+enum { kScalar = 0, kVector = 1, kStream = 2, kLines = 3, kStreamLong = 4 };
+
+template <int OP, int MAP, int TILE, int ROWS>
 static void launch_tile(const tri_plan *p, const ElemArgs &args, hipStream_t s)
 {
     const dim3 grid(p->gx, p->gy);
-    constexpr int NT = ElemShape<TILE, VECTOR>::NT;
-    if constexpr (OP == TRI_OP_AXPYT_F32)
-        k_axpyt<MAP, TILE, VECTOR><<<grid, NT, 0, s>>>(args);
-    else if constexpr (OP == TRI_OP_EDM4_F32)
-        k_edm4<MAP, TILE, VECTOR><<<grid, NT, 0, s>>>(args);
-    else
-        k_xormul<MAP, TILE, VECTOR><<<grid, NT, 0, s>>>(args);
+    if constexpr (ROWS == kLines && OP != TRI_OP_AXPYT_F32) {
+        static_assert(TILE >= 32, "whole lines");
+        k_lines<OP, MAP, TILE><<<grid, 8 * TILE, 0, s>>>(args);
+    } else {
+        constexpr bool VECTOR = ROWS != kScalar;
+        constexpr bool STREAM = ROWS == kStream || ROWS == kStreamLong;
+        constexpr int NT = ElemShape<TILE, VECTOR>::NT;
+        if constexpr (OP == TRI_OP_AXPYT_F32)
+            k_axpyt<MAP, TILE, VECTOR, STREAM><<<grid, NT, 0, s>>>(args);
+        else if constexpr (OP == TRI_OP_EDM4_F32)
+            k_edm4<MAP, TILE, VECTOR, STREAM, ROWS != kStreamLong><<<grid, NT, 0, s>>>(args);
+        else
+            k_xormul<MAP, TILE, VECTOR, STREAM><<<grid, NT, 0, s>>>(args);
+    }
 }
 
-template <int OP, int MAP, bool VECTOR>
+template <int OP, int MAP, int ROWS>
 static bool dispatch_tile(const tri_plan *p, const ElemArgs &args, hipStream_t s)
 {
-    switch (p->tile) {
-    case 8: launch_tile<OP, MAP, 8, VECTOR>(p, args, s); return true;
-    case 16: launch_tile<OP, MAP, 16, VECTOR>(p, args, s); return true;
-    case 32: launch_tile<OP, MAP, 32, VECTOR>(p, args, s); return true;
-    case 64: launch_tile<OP, MAP, 64, VECTOR>(p, args, s); return true;
-    case 128: launch_tile<OP, MAP, 128, VECTOR>(p, args, s); return true;
+    // xormul and edm4 take lines from tile 32 and the other misaligned forms
+    // below it
+    constexpr bool big = OP == TRI_OP_AXPYT_F32 || ROWS >= kStream;
+    if constexpr (ROWS != kLines) {
+        switch (p->tile) {
+        case 8: launch_tile<OP, MAP, 8, ROWS>(p, args, s); return true;
+        case 16: launch_tile<OP, MAP, 16, ROWS>(p, args, s); return true;
+        }
+    }
+    if constexpr (big) {
+        switch (p->tile) {
+        case 32: launch_tile<OP, MAP, 32, ROWS>(p, args, s); return true;
+        case 64: launch_tile<OP, MAP, 64, ROWS>(p, args, s); return true;
+        case 128: launch_tile<OP, MAP, 128, ROWS>(p, args, s); return true;
+        }
     }
     return false;
 }
@@ -686,30 +839,53 @@ static bool dispatch_axpyt_strip(const tri_plan *p, const ElemArgs &args, hipStr
     return true;
 }
 
-template <int OP, bool VECTOR>
+template <int OP, int ROWS>
 static bool dispatch_map(const tri_plan *p, const ElemArgs &args, hipStream_t s)
 {
-    // strips of tiles 16 and 32 (16-byte vectors, tile maps)
-    if constexpr (OP == TRI_OP_AXPYT_F32 && VECTOR) {
-        if ((p->tile == 16 || p->tile == 32) && strip_flag_len(p->flags) && p->map != TRI_MAP_UTM) {
-            switch (p->map) {
-            case TRI_MAP_BB: return dispatch_axpyt_strip<MAP_BB>(p, args, s);
-            case TRI_MAP_RB: return dispatch_axpyt_strip<MAP_RB>(p, args, s);
-            case TRI_MAP_REC: return dispatch_axpyt_strip<MAP_REC>(p, args, s);
-            case TRI_MAP_LAMBDA: return dispatch_axpyt_strip<MAP_LAMBDA>(p, args, s);
-            }
-        }
-    }
     switch (p->map) {
-    case TRI_MAP_BB: return dispatch_tile<OP, MAP_BB, VECTOR>(p, args, s);
-    case TRI_MAP_RB: return dispatch_tile<OP, MAP_RB, VECTOR>(p, args, s);
-    case TRI_MAP_REC: return dispatch_tile<OP, MAP_REC, VECTOR>(p, args, s);
-    case TRI_MAP_LAMBDA: return dispatch_tile<OP, MAP_LAMBDA, VECTOR>(p, args, s);
-    case TRI_MAP_UTM:
+    case TRI_MAP_BB: return dispatch_tile<OP, MAP_BB, ROWS>(p, args, s);
+    case TRI_MAP_RB: return dispatch_tile<OP, MAP_RB, ROWS>(p, args, s);
+    case TRI_MAP_REC: return dispatch_tile<OP, MAP_REC, ROWS>(p, args, s);
+    case TRI_MAP_LAMBDA: return dispatch_tile<OP, MAP_LAMBDA, ROWS>(p, args, s);
+    }
+    return false;
+}
+
+static bool axpyt_strips(const tri_plan *p, const ElemArgs &args, hipStream_t s)
+{
+    switch (p->map) {
+    case TRI_MAP_BB: return dispatch_axpyt_strip<MAP_BB>(p, args, s);
+    case TRI_MAP_RB: return dispatch_axpyt_strip<MAP_RB>(p, args, s);
+    case TRI_MAP_REC: return dispatch_axpyt_strip<MAP_REC>(p, args, s);
+    case TRI_MAP_LAMBDA: return dispatch_axpyt_strip<MAP_LAMBDA>(p, args, s);
+    }
+    return false;
+}
+
+template <int OP>
+static bool dispatch_rows(const tri_plan *p, ElemArgs args, bool vector, bool lines, hipStream_t s)
+{
+    if (p->map == TRI_MAP_UTM) {
         k_elem_utm<OP><<<dim3(p->gx, p->gy), kUtmThreads, 0, s>>>(args, p->elements);
         return true;
     }
-    return false;
+    // strips of tiles 16 and 32 (16-byte vectors, tile maps)
+    if (OP == TRI_OP_AXPYT_F32 && vector && (p->tile == 16 || p->tile == 32) &&
+        strip_flag_len(p->flags))
+        return axpyt_strips(p, args, s);
+    if (lines) {
+        // matrices that the L2s hold: cached accesses save a tenth (n = 2048,
+        // tile 32 4.9 -> 4.2 us, n = 4096 18.0 -> 16.3; n = 8192 77 -> 85)
+        if (OP == TRI_OP_AXPYT_F32 && p->elements * 12 <= (128ll << 20))
+            return dispatch_map<OP, kVector>(p, args, s);
+        // outputs beyond the memory-side cache (256 MB): see k_edm4
+        if constexpr (OP == TRI_OP_EDM4_F32)
+            if (p->elements * 4 > (256ll << 20)) return dispatch_map<OP, kStreamLong>(p, args, s);
+        return dispatch_map<OP, kStream>(p, args, s);
+    }
+    if (OP != TRI_OP_AXPYT_F32 && p->tile >= 32) return dispatch_map<OP, kLines>(p, args, s);
+    if (p->map == TRI_MAP_LAMBDA) args.g = plan_tile_grid_swizzled(p);
+    return vector ? dispatch_map<OP, kVector>(p, args, s) : dispatch_map<OP, kScalar>(p, args, s);
 }
 
 }  // namespace trimap
@@ -744,16 +920,13 @@ extern "C" tri_status tri_launch_elementwise(const tri_plan *p, int op, const vo
 
     ElemArgs args{plan_tile_grid(p), (int32_t)p->n, ld, x, y, c, a};
     hipStream_t s = (hipStream_t)stream;
+    // every row of every matrix on a 128-byte line
+    bool lines = ld % 32 == 0 && (cx & 127) == 0;
+    if (op == TRI_OP_AXPYT_F32) lines = lines && ((xx | yx) & 127) == 0;
     bool ok;
-    if (op == TRI_OP_AXPYT_F32)
-        ok = vector ? dispatch_map<TRI_OP_AXPYT_F32, true>(p, args, s)
-                    : dispatch_map<TRI_OP_AXPYT_F32, false>(p, args, s);
-    else if (op == TRI_OP_EDM4_F32)
-        ok = vector ? dispatch_map<TRI_OP_EDM4_F32, true>(p, args, s)
-                    : dispatch_map<TRI_OP_EDM4_F32, false>(p, args, s);
-    else
-        ok = vector ? dispatch_map<TRI_OP_XORMUL_I32, true>(p, args, s)
-                    : dispatch_map<TRI_OP_XORMUL_I32, false>(p, args, s);
+    if (op == TRI_OP_AXPYT_F32) ok = dispatch_rows<TRI_OP_AXPYT_F32>(p, args, vector, lines, s);
+    else if (op == TRI_OP_EDM4_F32) ok = dispatch_rows<TRI_OP_EDM4_F32>(p, args, vector, lines, s);
+    else ok = dispatch_rows<TRI_OP_XORMUL_I32>(p, args, vector, lines, s);
     if (!ok) return fail(TRI_E_UNSUPPORTED, "tri_launch_elementwise: tile %d", p->tile);
     TRI_HIP(hipGetLastError());
     return TRI_OK;

@@ -50,9 +50,8 @@ static bool grid_1d(uint64_t blocks, uint32_t &gx, uint32_t &gy)
     return true;
 }
 
-static TileGrid tile_grid(const tri_plan *p)
+static TileGrid tile_grid(const tri_plan *p, uint32_t f)
 {
-    uint32_t f = p->flags;
     if (p->map == TRI_MAP_LAMBDA && p->gy == 1 && (uint64_t)p->gx == (uint64_t)p->T &&
         p->T <= (1ll << 24) &&
         (f & ~(uint32_t)(TRI_FLAG_XCD_SWIZZLE | TRI_FLAG_STRIP_MASK | TRI_FLAG_STRIP_COLS | TRI_FLAG_STRIP_ALIGN |
@@ -264,7 +263,7 @@ tri_status tri_map_dump(const tri_plan *p, int64_t *dev_out, void *stream)
     if (p->blocks == 0) return TRI_OK;
     hipStream_t s = (hipStream_t)stream;
     const dim3 grid(p->gx, p->gy);
-    const TileGrid g = tile_grid(p);
+    const TileGrid g = tile_grid(p, p->flags);
     switch (p->map) {
     case TRI_MAP_BB: k_map_dump<MAP_BB><<<grid, 64, 0, s>>>(g, dev_out); break;
     case TRI_MAP_RB: k_map_dump<MAP_RB><<<grid, 64, 0, s>>>(g, dev_out); break;
@@ -299,5 +298,12 @@ tri_status tri_lambda_eval(const uint64_t *dev_omega, int64_t count, int include
 }  // extern "C"
 
 namespace trimap {
-TileGrid plan_tile_grid(const tri_plan *p) { return tile_grid(p); }
+TileGrid plan_tile_grid(const tri_plan *p) { return tile_grid(p, p->flags); }
+
+// The plan's tile grid in the swizzled order of omega, whatever its own order.
+TileGrid plan_tile_grid_swizzled(const tri_plan *p)
+{
+    return tile_grid(p, (p->flags & ~(uint32_t)(TRI_FLAG_ORDER_REVERSE | TRI_FLAG_ORDER_PAIRS)) |
+                            TRI_FLAG_XCD_SWIZZLE);
+}
 }  // namespace trimap

@@ -49,6 +49,30 @@ def test_edm4_bit_exact(map_name, tile):
             assert (got.view(np.uint32) == exp.view(np.uint32)).all(), (map_name, tile, n, ld)
 
 
+@pytest.mark.parametrize("tile", [8, 64, 128])
+@pytest.mark.parametrize("scale", [-80, -49, -47, 0, 46, 49, 70])
+def test_edm4_square_root_ranges(tile, scale):
+    """Squares below, around, inside and above the range of the short square
+    root, zeros, infinities and NaN among them."""
+    tm = _tm()
+    n = 200
+    P = inputs.points4(n, seed=scale + 100) * np.float32(2.0 ** scale)
+    P[7] = P[3]
+    for odd in (False, True):
+        if odd:
+            P[20, 0], P[90, 3], P[150, 1] = np.inf, np.nan, -np.inf
+        for ld in (224, 201):
+            C0 = np.zeros((n, ld), dtype=np.float32)
+            exp = C0.copy()
+            oracle.edm4(P, exp)
+            note("edm4 ranges", tile, scale, odd, ld)
+            c = dev(C0)
+            tm.Plan(n, tile, "lambda").elementwise(tm.OP_EDM4_F32, dev(P), None, c, ld=ld)
+            got = host(c)
+            same = (got.view(np.uint32) == exp.view(np.uint32)) | (np.isnan(got) & np.isnan(exp))
+            assert same.all(), (tile, scale, odd, ld)
+
+
 def test_edm4_rejects_unaligned_points():
     import torch
     tm = _tm()

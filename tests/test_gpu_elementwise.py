@@ -103,6 +103,53 @@ def test_axpyt_f32_strips_bit_exact(map_name, tile, strip, flags):
         assert (got.view(np.uint32) == exp.view(np.uint32)).all(), (map_name, tile, strip, flags, n)
 
 
+@pytest.mark.parametrize("map_name", ["bb", "rb", "lambda"])
+@pytest.mark.parametrize("tile", [16, 32, 64, 128])
+@pytest.mark.parametrize("shift,extra", [(0, 1), (1, 0), (3, 4), (31, 7), (16, 32), (4, 4), (0, 16)])
+def test_rows_off_the_lines_bit_exact(map_name, tile, shift, extra):
+    """Matrices whose rows do not start on 128-byte lines: the first element
+    `shift` floats past one, a pitch of any residue; every operation, the
+    cells around the matrix and above the diagonal untouched."""
+    import torch
+    tm = _tm()
+    for n in (1, 31, 33, 64, 129, 300):
+        ld = padded_ld(n, 32) + extra
+        note("rows off the lines", map_name, tile, shift, ld, n)
+        p = tm.Plan(n, tile, map_name, flags=tm.FLAG_ORDER_PAIRS if map_name == "lambda" else 0)
+
+        def at(m):
+            raw = torch.full((shift + m.size + 8,), 7, dtype=torch.int32, device="cuda")
+            raw[shift:shift + m.size] = dev(np.ascontiguousarray(m).view(np.int32)).reshape(-1)
+            return raw, raw[shift:shift + m.size].view(n, ld)
+
+        def check(raw, exp, op):
+            got = host(raw)
+            assert (got[:shift] == 7).all() and (got[shift + exp.size:] == 7).all(), op
+            assert (got[shift:shift + exp.size] == exp.view(np.int32).reshape(-1)).all(), (op, n)
+
+        A, B, C0 = inputs.int_elementwise(n, seed=n + shift, ld=ld)
+        exp = C0.copy()
+        oracle.c0(A, B, exp)
+        raw, c = at(C0)
+        p.elementwise(tm.OP_XORMUL_I32, dev(A), dev(B), c, ld=ld)
+        check(raw, exp, "xormul")
+
+        a, X, Y, C0 = inputs.f32_elementwise(n, seed=n + shift, ld=ld)
+        exp = C0.copy()
+        oracle.c1(a, X, Y, exp, n=n)
+        raw, c = at(C0)
+        p.elementwise(tm.OP_AXPYT_F32, at(X)[1].view(torch.float32), at(Y)[1].view(torch.float32),
+                      c.view(torch.float32), ld=ld, a=float(a))
+        check(raw, exp, "axpyt")
+
+        P = inputs.points4(n, seed=n)
+        exp = C0.copy()
+        oracle.edm4(P, exp)
+        raw, c = at(C0)
+        p.elementwise(tm.OP_EDM4_F32, dev(P), None, c.view(torch.float32), ld=ld)
+        check(raw, exp, "edm4")
+
+
 def test_band_strips_need_four_tiles():
     """Two-row band strips need strips of at least 4 tiles in the
     elementwise kernels; the distance map and the stencil refuse them."""
