@@ -151,17 +151,42 @@ static EdmWs edm_ws_layout(int64_t n, int64_t d)
     return w;
 }
 
-// Column sums of blocks of kColsumRows rows, in row order (deterministic).
+// Column sums of blocks of kColsumRows rows (deterministic), eight loads in
+// flight per thread.  Up to 128 (padded) dimensions the block's rows are
+// shared by 256 / dp groups of threads, each in row order, and their sums added
+// in group order (one group for all 64 rows took 7.5 us whatever n).
+constexpr int kColsumGroups = 8;  // at most
+
 __global__ void __launch_bounds__(256) k_edm_colsum(const float *x, int32_t n, int32_t d,
                                                     int64_t ldx, int32_t dp, float *partial)
 {
-    const int32_t r0 = blockIdx.x * kColsumRows;
-    const int32_t r1 = min(n, r0 + kColsumRows);
-    for (int32_t k = threadIdx.x; k < dp; k += 256) {
+    __shared__ float red[kColsumGroups * 32];  // groups * dp = 256 values
+    const int32_t groups = dp <= kStripMaxDims ? 256 / dp : 1;  // dp is a power of two there
+    const int32_t share = kColsumRows / groups, stride = 256 / groups;
+    const int32_t g = threadIdx.x / stride;
+    const int32_t r0 = blockIdx.x * kColsumRows + g * share;
+    for (int32_t k = threadIdx.x % stride; k < dp; k += stride) {
         float s = 0.f;
-        if (k < d)
-            for (int32_t r = r0; r < r1; ++r) s += x[(int64_t)r * ldx + k];
-        partial[(int64_t)blockIdx.x * dp + k] = s;
+        if (k < d && r0 < n) {
+            for (int32_t r = 0; r < share; r += 8) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = x[(int64_t)min(r0 + r + u, n - 1) * ldx + k];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += r0 + r + u < n ? v[u] : 0.f;
+            }
+        }
+        if (groups == 1) {
+            partial[(int64_t)blockIdx.x * dp + k] = s;
+        } else {
+            red[threadIdx.x] = s;
+            __syncthreads();
+            if (g == 0) {
+                for (int32_t q = 1; q < groups; ++q) s += red[q * stride + k];
+                partial[(int64_t)blockIdx.x * dp + k] = s;
+            }
+        }
     }
 }
 
@@ -234,6 +259,34 @@ __device__ __forceinline__ float direct_d2(const float *x, int64_t ldx, int32_t 
     // more loads in flight here cost the whole kernel registers
 #pragma unroll 1
     for (int32_t k = 0; k < d; ++k) {
+        const float df = xi[k] - xj[k];
+        s = __builtin_fmaf(df, df, s);
+    }
+    return s;
+}
+
+// The same sum in the same order with the loads of eight dimensions in flight,
+// for kernels that have the registers at that point.
+__device__ __forceinline__ float direct_d2_wide(const float *x, int64_t ldx, int32_t d, int32_t i,
+                                                int32_t j)
+{
+    const float *xi = x + (int64_t)i * ldx, *xj = x + (int64_t)j * ldx;
+    float s = 0.f;
+    int32_t k = 0;
+    for (; k + 8 <= d; k += 8) {
+        float a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            a[u] = xi[k + u];
+            b[u] = xj[k + u];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float df = a[u] - b[u];
+            s = __builtin_fmaf(df, df, s);
+        }
+    }
+    for (; k < d; ++k) {
         const float df = xi[k] - xj[k];
         s = __builtin_fmaf(df, df, s);
     }
@@ -434,7 +487,7 @@ __device__ __forceinline__ void edm_epilogue(const EdmMfmaArgs &p, f32x16 (&acc)
             const int32_t j = C0 + 32 * b + lr;
             if (i < n && j < i)
                 __builtin_nontemporal_store(
-                    __builtin_amdgcn_sqrtf(direct_d2(p.x, p.ldx, p.d, i, j)),
+                    __builtin_amdgcn_sqrtf(direct_d2_wide(p.x, p.ldx, p.d, i, j)),
                     (float *)(ob + (((uint32_t)((i - R0) * (i + R0 - 1)) / 2u + (uint32_t)j) << 2)));
         }
     }
@@ -495,7 +548,7 @@ __device__ __forceinline__ void edm_distances_to_lds(const EdmMfmaArgs &p, f32x1
             const int32_t i = R0 + dr + 4 * (l >> 5);
             const int32_t j = C0 + 32 * b + lr;
             if (i < n && j < i)
-                Dw[dr * kDStride + 32 * b] = __builtin_amdgcn_sqrtf(direct_d2(p.x, p.ldx, p.d, i, j));
+                Dw[dr * kDStride + 32 * b] = __builtin_amdgcn_sqrtf(direct_d2_wide(p.x, p.ldx, p.d, i, j));
         }
     }
 }
@@ -665,35 +718,68 @@ __device__ __forceinline__ void split3(float v, __bf16 &h, __bf16 &m, __bf16 &lo
     lo = (__bf16)(r1 - (float)m);
 }
 
-// Pre-pass in fragment order: one thread per point p < np centres its
-// coordinates, splits them into BF16 hi and lo (hi only for single BF16),
-// and sums the norm of the rounded operands, hi.hi + 2 hi.lo, in dimension
-// order.  It then writes the two planes of the norm step: as a column
-// operand (dimensions 0..5: 1, 1, 1 and -n / 2 in three parts) and as a row
-// operand (the three parts, then 1, 1, 1); dimensions 8..15 are zero.
-// Points beyond n get zeros (their norm steps carry no norm).
-template <bool SPLIT, int S>
+// Pre-pass in fragment order: a workgroup takes one group of 32 points p < np,
+// stages its coordinates, centred, in LDS (row-contiguous loads, all of a
+// thread's in flight), and eight threads per point split them into BF16 hi
+// and lo (hi only for single BF16), eight dimensions at a time, and sum the
+// norm of the rounded operands, hi.hi + 2 hi.lo, in dimension order, the
+// eight sums added in order.  Four threads per point then write the two
+// planes of the norm step: as a column operand (dimensions 0..5: 1, 1, 1 and
+// -n / 2 in three parts) and as a row operand (the three parts, then 1, 1,
+// 1); dimensions 8..15 are zero.  Points beyond n get zero coordinates and a
+// huge norm.  HERE: the mean is summed here, from the nb column sums,
+// instead of by a launch of its own (few of them: nb <= kMeanHere).
+// One thread per point left n = 2000 nine workgroups: 13 us at d = 64, 24 at
+// d = 128; in this form 4.4 and 5.9, and n = 8000, d = 64 14.5 -> 4.8.
+constexpr int kMeanHere = 64;
+
+template <bool SPLIT, int S, bool HERE>
 __global__ void __launch_bounds__(256) k_edm_frag(const float *x, int32_t n, int32_t d,
-                                                  int64_t ldx, int32_t np, const float *mean,
+                                                  int64_t ldx, const float *mean, int32_t nb,
                                                   bf16x8 *frag)
 {
     constexpr int P = SPLIT ? 2 : 1;
-    constexpr int KP = S * P;
-    const int32_t p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= np) return;
-    const bool live = p < n;
-    const int64_t grp = (int64_t)(p >> 5) * edm_group_vecs(KP) + (p & 31);
+    constexpr int KP = S * P, DP = 16 * S, LD = DP + 4, PER = 32 * DP / 256;
+    __shared__ __attribute__((aligned(16))) float xs[32 * LD];
+    __shared__ float mu[DP], nrm[8][32];
+    const int t = threadIdx.x;
+    const int32_t p0 = blockIdx.x * 32;
+    float v[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int e = t + 256 * u, row = e / DP, k = e % DP;
+        v[u] = x[(int64_t)min(p0 + row, n - 1) * ldx + min(k, d - 1)];
+    }
+    if (t < DP) {
+        if constexpr (HERE) {  // `mean` holds the column sums
+            float s = 0.f;
+#pragma unroll 8
+            for (int32_t b = 0; b < nb; ++b) s += mean[(int64_t)b * DP + t];
+            mu[t] = s / (float)n;
+        } else {
+            mu[t] = mean[t];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int e = t + 256 * u, row = e / DP, k = e % DP;
+        xs[row * LD + k] = p0 + row < n && k < d ? v[u] - mu[k] : 0.f;
+    }
+    __syncthreads();
+
+    const int q = t & 31, w = t >> 5;  // point, its share of the dimensions
+    bf16x8 *const grp = frag + (int64_t)blockIdx.x * edm_group_vecs(KP) + q;
     float acc = 0.f;
+    constexpr int NV = 2 * S / 8 > 0 ? 2 * S / 8 : 1;  // vectors per thread (S = 2: half the threads)
+    if (w < 2 * S) {
 #pragma unroll
-    for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int u = 0; u < NV; ++u) {
+            const int vi = NV * w + u;  // dimensions 8 vi .. 8 vi + 7: k-step vi / 2, half vi % 2
             bf16x8 hv, lv;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int32_t k = 16 * s + 8 * h + e;
-                float c = 0.f;
-                if (live && k < d) c = x[(int64_t)p * ldx + k] - mean[k];
+                const float c = xs[q * LD + 8 * vi + e];
                 const __bf16 hb = (__bf16)c;
                 const float hf = (float)hb;
                 const __bf16 lb = (__bf16)(c - hf);
@@ -703,20 +789,26 @@ __global__ void __launch_bounds__(256) k_edm_frag(const float *x, int32_t n, int
                 if (SPLIT) acc = __builtin_fmaf(hf, hf, __builtin_fmaf(2.f * hf, lf, acc));
                 else acc = __builtin_fmaf(hf, hf, acc);
             }
-            frag[grp + ((s * P) * 2 + h) * 32] = hv;
-            if (SPLIT) frag[grp + ((s * P + 1) * 2 + h) * 32] = lv;
+            grp[((vi >> 1) * P * 2 + (vi & 1)) * 32] = hv;
+            if (SPLIT) grp[(((vi >> 1) * P + 1) * 2 + (vi & 1)) * 32] = lv;
         }
-    __bf16 nh, nm, nl;
-    split3(-0.5f * acc, nh, nm, nl);
-    const __bf16 one = (__bf16)1.f;
-    bf16x8 col{}, row{};
-    col[0] = one; col[1] = one; col[2] = one; col[3] = nh; col[4] = nm; col[5] = nl;
-    row[0] = nh; row[1] = nm; row[2] = nl; row[3] = one; row[4] = one; row[5] = one;
-    if (!live) col = row = bf16x8{};
-    frag[grp + (KP * 2) * 32] = col;
-    frag[grp + (KP * 2 + 1) * 32] = bf16x8{};
-    frag[grp + ((KP + 1) * 2) * 32] = row;
-    frag[grp + ((KP + 1) * 2 + 1) * 32] = bf16x8{};
+    }
+    nrm[w][q] = acc;
+    __syncthreads();
+    if (w < 4) {  // plane w of the norm steps' four
+        float sum = 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += nrm[u][q];
+        __bf16 nh, nm, nl;
+        // points beyond n lie far from every point: a zero norm would make all
+        // their pairs near (n = 2000: 10 us of sorting them out again)
+        split3(p0 + q < n ? -0.5f * sum : -1e30f, nh, nm, nl);
+        const __bf16 one = (__bf16)1.f;
+        bf16x8 o{};
+        if (w == 0) { o[0] = one; o[1] = one; o[2] = one; o[3] = nh; o[4] = nm; o[5] = nl; }
+        if (w == 2) { o[0] = nh; o[1] = nm; o[2] = nl; o[3] = one; o[4] = one; o[5] = one; }
+        grp[(KP * 2 + w) * 32] = o;
+    }
 }
 
 // The distance from an accumulator holding -d^2 / 2: d^2 = -2 acc exactly.
@@ -738,6 +830,12 @@ struct EdmLinesArgs {
     float thr;  // fix-up threshold on d^2
 };
 
+// Near pairs a wave lists for the strip's end.  Recomputed where they are found,
+// one dimension at a time (the kernel has no registers to spare there), each
+// costs d dependent loads: 16 us at d = 64, which was most of a small launch
+// (n = 2000 20 us, of which 136 workgroups had a few of the near-duplicates).
+constexpr int kNearCap = 128;
+
 template <int MAP, bool SPLIT, int S>
 __global__ void __launch_bounds__(256, 2) k_edm_lines(EdmLinesArgs a)
 {
@@ -749,6 +847,9 @@ __global__ void __launch_bounds__(256, 2) k_edm_lines(EdmLinesArgs a)
     // plane KP the norm step
     __shared__ bf16x8 sB0[(KP + 1) * 2 * 64];
     __shared__ bf16x8 sB1[(KP + 1) * 2 * 64];
+    // near pairs (i, j) of each wave, recomputed at the strip's end
+    __shared__ int2 snear[4][kNearCap];
+    __shared__ int32_t snear_n[4];
 
     const int t = threadIdx.x, l = t & 63, lo = l & 31, hf = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -825,6 +926,8 @@ __global__ void __launch_bounds__(256, 2) k_edm_lines(EdmLinesArgs a)
     stage_half(sB0, bj, 0);
     stage_half(sB1, bj, 1);
     set_rows(bi);
+    if (l == 0) snear_n[w] = 0;
+    int32_t listed = 0;  // near pairs in the wave's list
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
 
     f32x16 carry{};           // distances of the previous tile's block 3
@@ -1014,10 +1117,20 @@ __global__ void __launch_bounds__(256, 2) k_edm_lines(EdmLinesArgs a)
                 // loads count them)
                 asm volatile("" ::: "memory");
                 const bool anynear = __any((near | (carry_ok ? carry_near : 0u)) != 0);
+                // the tile's near pairs go to the list when they fit, else they
+                // are recomputed below (at most as many pairs as near bits)
+                bool list = false;
+                if (anynear) {
+                    int32_t c = __builtin_popcountll(near) +
+                                (carry_ok ? __builtin_popcount(carry_near) : 0);
+#pragma unroll
+                    for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
+                    list = listed + c <= kNearCap;
+                }
                 // lines 2 (blocks 1, 2) and 3 (blocks 2, 3): deferred into the
                 // next tile's first pass when it continues this tile row and
-                // no near square waits for its fix-up
-                const bool defer = full && more && nbi == bi && !anynear;
+                // no near square is recomputed before that
+                const bool defer = full && more && nbi == bi && (!anynear || list);
                 if (full) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
@@ -1068,12 +1181,21 @@ __global__ void __launch_bounds__(256, 2) k_edm_lines(EdmLinesArgs a)
                         }
                         if (!inside(r, jt)) continue;
                         const int32_t i = R0 + 32 * w + 8 * (r >> 2) + 4 * hf + (r & 3);
+                        if (list) {
+                            snear[w][atomicAdd(&snear_n[w], 1)] = make_int2(i, CW + jt);
+                            continue;
+                        }
                         const uint32_t ro = (uint32_t)((i - R0) * (i + R0 - 1)) / 2u;
                         *(float *)(obt + 4u * (ro + (uint32_t)jt)) =
                             __builtin_amdgcn_sqrtf(direct_d2(a.x, a.ldx, a.d, i, CW + jt));
                     }
-                    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-                    waited = true;
+                    if (list) {
+                        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+                        listed = __builtin_amdgcn_readfirstlane(snear_n[w]);
+                    } else {
+                        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+                        waited = true;
+                    }
                 }
                 carry = D[1];
             }
@@ -1090,6 +1212,15 @@ __global__ void __launch_bounds__(256, 2) k_edm_lines(EdmLinesArgs a)
         k = nk;
         bi = nbi;
         bj = nbj;
+    }
+    // the wave's listed near pairs, over the values it has stored
+    if (listed) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        for (int32_t e = l; e < listed; e += 64) {
+            const int2 ij = snear[w][e];
+            a.out[(int64_t)ij.x * (ij.x - 1) / 2 + ij.y] =
+                __builtin_amdgcn_sqrtf(direct_d2_wide(a.x, a.ldx, a.d, ij.x, ij.y));
+        }
     }
 }
 
@@ -1465,12 +1596,17 @@ __global__ void __launch_bounds__(256, 1) k_edm_pipe(EdmLinesArgs a)
 // consecutive, so the carry passes from tile to tile).
 constexpr int32_t kEdmStripGroup = 1;
 
-// Tiles per strip: the plan's TRI_FLAG_STRIP, else enough strips for
-// several rounds of the GPU's workgroup slots and strips long enough that the
-// row operands loaded into registers serve several tiles.
+// Tiles per strip: the plan's TRI_FLAG_STRIP, halved while the strips would
+// leave some of the 512 resident workgroups without one (16 tiles: n = 2000, d
+// = 64 98 us, one 19; n = 8000 100, two 57); else enough strips for several
+// rounds of the GPU's workgroup slots and strips long enough that the row
+// operands loaded into registers serve several tiles.
 static int32_t strip_len(const tri_plan *p)
 {
-    if (const int32_t f = strip_flag_len(p->flags)) return f;
+    if (int32_t f = strip_flag_len(p->flags)) {
+        while (f > 1 && p->T / f < 512) f >>= 1;
+        return f;
+    }
     const uint64_t g = (uint64_t)p->T / 8192;
     return (int32_t)(g < 1 ? 1 : (g > 8 ? 8 : g));
 }
@@ -1510,15 +1646,29 @@ static bool edm_lines(const tri_plan *p, const EdmLinesArgs &a, int S, hipStream
     return false;
 }
 
+// The fragment pre-pass of np points; `partial` the nb column sums, `mean` the
+// mean when nb > kMeanHere.
+template <bool SPLIT, int S>
+static void edm_frag_shape(const float *x, int32_t n, int32_t d, int64_t ldx, int32_t np,
+                           const float *partial, int32_t nb, const float *mean, bf16x8 *frag,
+                           hipStream_t s)
+{
+    const dim3 grid((uint32_t)(np / 32));
+    if (nb <= kMeanHere)
+        k_edm_frag<SPLIT, S, true><<<grid, 256, 0, s>>>(x, n, d, ldx, partial, nb, frag);
+    else
+        k_edm_frag<SPLIT, S, false><<<grid, 256, 0, s>>>(x, n, d, ldx, mean, nb, frag);
+}
+
 template <bool SPLIT>
 static void edm_frag_launch(int S, const float *x, int32_t n, int32_t d, int64_t ldx, int32_t np,
-                            const float *mean, bf16x8 *frag, hipStream_t s)
+                            const float *partial, int32_t nb, const float *mean, bf16x8 *frag,
+                            hipStream_t s)
 {
-    const dim3 grid((uint32_t)((np + 255) / 256));
     switch (S) {
-    case 2: k_edm_frag<SPLIT, 2><<<grid, 256, 0, s>>>(x, n, d, ldx, np, mean, frag); break;
-    case 4: k_edm_frag<SPLIT, 4><<<grid, 256, 0, s>>>(x, n, d, ldx, np, mean, frag); break;
-    case 8: k_edm_frag<SPLIT, 8><<<grid, 256, 0, s>>>(x, n, d, ldx, np, mean, frag); break;
+    case 2: edm_frag_shape<SPLIT, 2>(x, n, d, ldx, np, partial, nb, mean, frag, s); break;
+    case 4: edm_frag_shape<SPLIT, 4>(x, n, d, ldx, np, partial, nb, mean, frag, s); break;
+    case 8: edm_frag_shape<SPLIT, 8>(x, n, d, ldx, np, partial, nb, mean, frag, s); break;
     }
 }
 
@@ -1607,12 +1757,13 @@ static tri_status edm_run(const tri_plan *p, const float *x, int64_t d, int64_t 
     const int32_t n = (int32_t)p->n, dd = (int32_t)d, dp = (int32_t)L.dp;
     const bool split = (mode == TRI_EDM_BF16X3);
     k_edm_colsum<<<dim3((uint32_t)L.nb), 256, 0, s>>>(x, n, dd, ldx, dp, partial);
-    k_edm_mean<<<dim3((uint32_t)dp), 256, 0, s>>>(partial, (int32_t)L.nb, n, dp, mean);
+    if (!L.S || L.nb > kMeanHere)
+        k_edm_mean<<<dim3((uint32_t)dp), 256, 0, s>>>(partial, (int32_t)L.nb, n, dp, mean);
     if (L.S) {
         bf16x8 *frag = (bf16x8 *)(w + L.hi);
         const int32_t np = (int32_t)L.np;
-        if (split) edm_frag_launch<true>(L.S, x, n, dd, ldx, np, mean, frag, s);
-        else edm_frag_launch<false>(L.S, x, n, dd, ldx, np, mean, frag, s);
+        if (split) edm_frag_launch<true>(L.S, x, n, dd, ldx, np, partial, (int32_t)L.nb, mean, frag, s);
+        else edm_frag_launch<false>(L.S, x, n, dd, ldx, np, partial, (int32_t)L.nb, mean, frag, s);
         TRI_HIP(hipGetLastError());
         EdmLinesArgs a{plan_tile_grid(p), StripGrid{}, n, dd, ldx, x, frag, out, fixup_thr};
         const bool ok = split ? edm_lines<true>(p, a, L.S, s) : edm_lines<false>(p, a, L.S, s);

@@ -452,3 +452,47 @@ def test_edm_mfma_full_size_strip_orders(mode, flags, plain_edm):
             assert (np.abs(g - e) <= 2.0 ** -7 * (nrm[r] + nrm[:r])).all(), r
     del out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("d", [8, 40, 128, 150])
+@pytest.mark.parametrize("near", ["few", "list full", "all"])
+def test_near_pairs_listed_and_not(mode, d, near):
+    """Pairs below the threshold: a few in a wave's strip (listed and
+    recomputed at its end), about as many as the list holds, and every pair
+    (recomputed where found).  Within a cluster the distance is the direct
+    FP32 one; the same bits whatever the strip length."""
+    import torch
+    tm = _tm()
+    rng = np.random.default_rng(d + mode)
+    n = 700
+    X = rng.random((n, d), dtype=np.float32)
+    if near == "few":
+        X[100:104] = X[90] + rng.random((4, d), dtype=np.float32) * np.float32(1e-3)
+        X[699] = X[0]
+    elif near == "list full":
+        X[::13] = X[0] + rng.random((len(X[::13]), d), dtype=np.float32) * np.float32(1e-3)
+    else:
+        X = X[:1] + rng.random((n, d), dtype=np.float32) * np.float32(1e-3)
+    thr = 1e-2
+    x = dev(X)
+    exact = np.sqrt(((X[:, None, :].astype(np.float64) - X[None]) ** 2).sum(-1))
+    i, j = np.tril_indices(n, -1)
+    want = exact[i, j]
+    first = None
+    for flags in (0, tm.FLAG_STRIP(0), tm.FLAG_STRIP(4) | tm.FLAG_STRIP_COLS):
+        p = tm.Plan(n, 128, "lambda", include_diag=False, flags=flags)
+        ws = torch.empty(p.edm_workspace_size(d, mode), dtype=torch.uint8, device="cuda")
+        out = torch.full((n * (n - 1) // 2,), -1.0, device="cuda")
+        note("near pairs", mode, d, near, flags)
+        p.edm(x, out, mode, fixup_thr=thr, ws=ws)
+        got = host(out)
+        close = want * want < 0.5 * thr
+        assert close.any()
+        # d FP32 squares and sums, the hardware square root (1 ulp)
+        assert (np.abs(got[close] - want[close]) <= want[close] * (d + 4) * 2.0 ** -24).all()
+        far = want * want > 2 * thr
+        assert (np.abs(got[far] - want[far]) <= want[far] * (1e-3 if mode == 1 else 2e-2)).all()
+        if first is None:
+            first = got
+        assert (got.view(np.uint32) == first.view(np.uint32)).all(), flags
