@@ -1078,12 +1078,12 @@ __device__ __forceinline__ void lds_read_rows(const float *src, float (&dst)[RB]
 // kEdmStageVec4: the same with 16-byte loads at 32-bit byte offsets from the
 // base (needs d and ldx multiples of 4, a 16-byte aligned x and
 // n * ldx * 4 < 2^31): a quarter of the loads and of their address
-// registers.
+// registers.  tid: the lane's number among the 256 that share the tile.
 enum { kEdmStageLoop = 0, kEdmStageScalar = 1, kEdmStageVec4 = 2 };
 
 template <int TILE, int STAGE = kEdmStageScalar>
 __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, int32_t bj,
-                                                  float *lds)
+                                                  float *lds, int tid)
 {
     using S = EdmF32Shape<TILE>;
     float *XI = lds;                  // [K][LD]
@@ -1092,7 +1092,7 @@ __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, 
     const int64_t ldx = p.ldx;
     const int32_t ri0 = 1 + bi * TILE;  // first row of the tile
     const int32_t cj0 = bj * TILE;      // first column of the tile
-    const int tx = threadIdx.x % S::TX, ty = threadIdx.x / S::TX;
+    const int tx = tid % S::TX, ty = tid / S::TX;
 
     float acc[S::RB][S::CB];
 #pragma unroll
@@ -1111,7 +1111,7 @@ __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, 
             f4v vi[PER], vj[PER];
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
-                const int idx = threadIdx.x + S::NT * u;
+                const int idx = tid + S::NT * u;
                 const int row = idx / KQ, kq = idx % KQ;
                 const int32_t k = min(k0 + 4 * kq, d - 4);
                 const int32_t ri = min(ri0 + row, n - 1), rj = min(cj0 + row, n - 1);
@@ -1120,7 +1120,7 @@ __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, 
             }
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
-                const int idx = threadIdx.x + S::NT * u;
+                const int idx = tid + S::NT * u;
                 const int row = idx / KQ, kq = idx % KQ;
                 const bool kin = k0 + 4 * kq < d;
                 const bool iin = kin && ri0 + row < n, jin = kin && cj0 + row < n;
@@ -1136,7 +1136,7 @@ __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, 
             float vi[PER], vj[PER];
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
-                const int idx = threadIdx.x + S::NT * u;
+                const int idx = tid + S::NT * u;
                 const int row = idx / S::K, kk = idx % S::K;
                 const int32_t k = min(k0 + kk, d - 1);
                 vi[u] = p.x[(int64_t)min(ri0 + row, n - 1) * ldx + k];
@@ -1144,14 +1144,14 @@ __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, 
             }
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
-                const int idx = threadIdx.x + S::NT * u;
+                const int idx = tid + S::NT * u;
                 const int row = idx / S::K, kk = idx % S::K;
                 const bool kin = k0 + kk < d;
                 XI[kk * S::LD + row] = (ri0 + row < n && kin) ? vi[u] : 0.f;
                 XJ[kk * S::LD + row] = (cj0 + row < n && kin) ? vj[u] : 0.f;
             }
         } else {
-            for (int idx = threadIdx.x; idx < TILE * S::K; idx += S::NT) {
+            for (int idx = tid; idx < TILE * S::K; idx += S::NT) {
                 const int row = idx / S::K, kk = idx % S::K;
                 const int32_t k = k0 + kk;
                 const int32_t gi = ri0 + row, gj = cj0 + row;
@@ -1188,6 +1188,13 @@ __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, 
             if (j < i) __builtin_nontemporal_store(__builtin_sqrtf(acc[a][c]), orow + j);
         }
     }
+}
+
+template <int TILE, int STAGE = kEdmStageScalar>
+__device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, int32_t bj,
+                                                  float *lds)
+{
+    edm_f32_tile_body<TILE, STAGE>(p, bi, bj, lds, (int)threadIdx.x);
 }
 
 }  // namespace trimap

@@ -78,6 +78,71 @@ def test_edm_fp32_padded_rows(tile):
         _check_rows(X, host(out), list(range(n)), _fp32_bound(d))
 
 
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("data", ["uniform", "clusters", "far off", "outliers", "tiny", "huge",
+                                  "wild"])
+def test_edm_fp32_matrix_cores(tile, data):
+    """FP32 mode around the dimensions from which it takes products (64), at
+    ragged dimensions, pitches and sides, against the exact distances of the
+    FP32 coordinates.  A pair is held to the direct sum's bound or, with d^2
+    at least 3/8 of the norms' sum S and an error of (d/8 + 4) U S from each
+    norm's sum, 4 U S from the rounding of the coordinates, 8 U S from their
+    split and 8 U S from the products' sum (in all at most (d/4 + 20) U S from
+    d = 32 on), to half of 8/3 (d/4 + 20) U."""
+    import torch
+    tm = _tm()
+    rng = np.random.default_rng(7)
+    for n, d, pad in ((2, 64, 0), (64, 63, 0), (65, 64, 1), (129, 65, 0), (130, 79, 3),
+                      (257, 80, 0), (300, 95, 2), (321, 130, 0), (200, 513, 0)):
+        X, _ = inputs.points(n, d, dup_frac=0.02, seed=4700 + n + d)
+        if data == "clusters":
+            X = rng.random((5, d))[rng.integers(0, 5, n)] + 0.01 * rng.random((n, d))
+        elif data == "far off":
+            X = X + 1e4
+        elif data == "outliers":
+            X[::37] *= np.float32(1e5)
+        elif data == "tiny":
+            X = X * 1e-15
+        elif data == "huge":
+            X = X * 1e15
+        elif data == "wild":
+            X = rng.standard_normal((n, d)) * 10.0 ** rng.uniform(-6, 6, (n, 1))
+        X = X.astype(np.float32)
+        W = np.full((n, d + pad), np.nan, dtype=np.float32)
+        W[:, :d] = X
+        note("edm fp32 products", tile, data, n, d, pad)
+        out = torch.full((n * (n - 1) // 2,), -1.0, dtype=torch.float32, device="cuda")
+        tm.Plan(n, tile, "lambda", include_diag=False).edm(dev(W)[:, :d], out, mode=tm.EDM_FP32)
+        tol = max(_fp32_bound(d), 4 / 3 * (d / 4 + 20) * U + 2 * U)
+        _check_rows(X, host(out), list(range(n)), tol)
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("where", ["one point", "sampled point"])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_edm_fp32_matrix_cores_not_finite(tile, where, value):
+    """A coordinate that is no finite number: its point's distances are not
+    finite either, and every other one is as exact as without it."""
+    import torch
+    tm = _tm()
+    n, d = 300, 72
+    X, _ = inputs.points(n, d, dup_frac=0.0, seed=4800)
+    bad = 1 if where == "sampled point" else 150
+    exp = oracle.edm_rows(X, list(range(n)))
+    X[bad, 5] = value
+    note("edm fp32 products, not finite", tile, where, value)
+    out = torch.full((n * (n - 1) // 2,), -1.0, dtype=torch.float32, device="cuda")
+    tm.Plan(n, tile, "lambda", include_diag=False).edm(dev(X), out, mode=tm.EDM_FP32)
+    got = host(out)
+    for i in range(1, n):
+        g = got[i * (i - 1) // 2: i * (i - 1) // 2 + i].astype(np.float64)
+        for j in range(i):
+            if bad in (i, j):
+                assert (np.isnan(g[j]) if np.isnan(value) else g[j] == np.inf), (i, j, g[j])
+            else:
+                assert abs(g[j] - exp[i][j]) <= _fp32_bound(2 * d) * exp[i][j], (i, j)
+
+
 @pytest.mark.slow
 @pytest.mark.parametrize("tile", [64, 128])
 def test_edm_fp32_full_size_sampled_rows(tile):
