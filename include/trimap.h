@@ -284,7 +284,7 @@ tri_status tri_launch_stencil(const tri_plan *plan, uint8_t *cur, uint8_t *nxt, 
  * n x d FP32 (1 <= d <= 4096), leading dimension ldx >= d, 4-byte aligned.
  * mode is a TRI_EDM_* value:
  *  - TRI_EDM_FP32: plan tile 16, 32, 64 or 128; no workspace (ws may be NULL).
- *    From 64 dimensions on, tiles of 64 and 128 take d^2 from FP32 norms about
+ *    From 32 dimensions on, tiles of 64 and 128 take d^2 from FP32 norms about
  *    a centre of the tile and a split product on the matrix cores, whose error
  *    is below the direct sum's; near pairs and tiles out of range are direct.
  *  - TRI_EDM_BF16X3 / TRI_EDM_BF16: plan tile 128; `out` 16-byte aligned

@@ -10,7 +10,7 @@
 // TRI_EDM_FP32: direct sum of squared differences, FP32 FMA, both point
 // blocks staged in LDS dimension-major so that a lane's 4x4 register block
 // reads broadcast / consecutive words.  Bound by the vector ALU (2 VALU ops
-// per pair and dimension).  From 64 dimensions on, at tiles of 64 and 128, the
+// per pair and dimension).  From 32 dimensions on, at tiles of 64 and 128, the
 // squares come from FP32 norms and a split Gram product that is nearer to the
 // exact distances than the direct sum (k_edm_gram).
 //
@@ -78,9 +78,9 @@ static bool edm_f32_map(const tri_plan *p, const EdmArgs &a, hipStream_t s)
 }
 
 // 16-byte staging for tiles of 64 and 128 where the coordinates allow it
-// (see kEdmStageVec4; measured at n = 65536, d = 128: 12.3 -> 11.4 ms at
-// tile 128, where it also lowers the registers from 193 to 126 and so
-// doubles the workgroups per CU; at tile 32 it is slower, 18.7 -> 21.4 ms).
+// (see kEdmStageVec4; measured with all of d = 128 here, n = 65536: 12.3 -> 11.4
+// ms at tile 128, where it also lowers the registers and so doubles the
+// workgroups per CU; at tile 32 it is slower, 18.7 -> 21.4 ms).
 static bool edm_f32(const tri_plan *p, const EdmArgs &a, hipStream_t s)
 {
     const EdmTile &t = a.t;
@@ -612,18 +612,22 @@ __device__ __forceinline__ void edm_store_tile_rows(const EdmMfmaArgs &p, const 
 // (ten tight clusters in random order, where every tile is: d = 128 770 -> 1020
 // us, without the early test 1130; a hundred clusters 760 -> 510).  Against 64 bits, uniform points with
 // 1 % near-duplicates, relative L2 and largest relative error, direct / here:
-// 6.5e-8 / 3.3e-8 and 3.2e-7 / 1.8e-7 at d = 64, 9.2e-8 / 4.0e-8 and 4.8e-7 /
-// 2.6e-7 at d = 128, 1.3e-7 / 3.5e-8 and 6.4e-7 / 2.5e-7 at d = 256; clusters of
-// 0.6 times their centres' spread 9.1e-8 / 4.0e-8 and 4.5e-7 / 3.7e-7.  Hence
-// the line at 64: at d = 32 the largest error would be larger than the direct
-// one (3.2e-7 against 2.6e-7).
+// 4.6e-8 / 3.9e-8 and 2.4e-7 / 2.6e-7 at d = 24, 5.2e-8 / 3.9e-8 and 2.9e-7 /
+// 2.4e-7 at d = 32, 6.4e-8 / 3.4e-8 and 3.7e-7 / 2.2e-7 at d = 63, 9.2e-8 /
+// 4.0e-8 and 4.8e-7 / 2.6e-7 at d = 128, 1.3e-7 / 3.5e-8 and 6.4e-7 / 2.5e-7 at
+// d = 256; d = 128 in clusters of 0.6 times their centres' spread 9.1e-8 /
+// 4.0e-8 and 4.5e-7 / 3.7e-7.  Hence the line at 32: below it the largest error
+// would be larger than the direct sum's.
 //
 // Work.  The direct form is bound by two vector operations per pair and
 // dimension.  Here they are about 5 per staged coordinate and 10 per pair, and
 // with the products (half as long, on the matrix cores, partly in their shadow)
 // and the power limit's clock they bound the kernel.  n = 16384: d = 128 706 ->
 // 234 us (tile 128) and 770 -> 288 us (tile 64), d = 64 404 -> 172 us; n = 10007,
-// d = 256 515 -> 143 us; n = 2000, d = 128 26.0 -> 11.4 us.  Tried in its place,
+// d = 256 515 -> 143 us; n = 2000, d = 128 26.0 -> 11.4 us.  Below d = 64 against
+// the direct form as it is now, tile 64 / 128: n = 16384, d = 32 247 -> 172 /
+// 233 -> 158 us, d = 50 379 -> 201 / 380 -> 174 us; n = 257, d = 32 6.8 -> 6.3 /
+// 16.0 -> 9.0 us; n = 2000, d = 32 9.9 -> 10.1 / 17.4 -> 10.1 us.  Tried in its place,
 // d = 128: FP32 products (v_mfma_f32_32x32x2_f32, which shares the vector
 // units: no overlap) 358 us; three BF16 parts, six products, 288 us.
 //
@@ -636,7 +640,7 @@ __device__ __forceinline__ void edm_store_tile_rows(const EdmMfmaArgs &p, const 
 // or two tiles write meet in its L2 (d = 64: 288 -> 172 us; either alone 209 and
 // 267 us).
 // ---------------------------------------------------------------------------
-constexpr int kGramMinDims = 64;
+constexpr int kGramMinDims = 32;
 constexpr float kGramNear = 0.375f;
 constexpr int kGramK = 16;         // dimensions per staged chunk
 constexpr int kGramLaneNear = 4;   // near pairs per lane (of 32 or 16) that a tile may hold
@@ -2108,7 +2112,7 @@ static tri_status edm_run(const tri_plan *p, const float *x, int64_t d, int64_t 
         // from kGramMinDims on the matrix cores are both nearer and faster (see
         // k_edm_gram); its offsets within a tile are 32 bits, 128 rows of ldx
         const bool gram = p->tile >= 64 && d >= kGramMinDims && ldx <= (1 << 22);
-        if (gram) a.g = plan_tile_grid_swizzled(p);
+        a.g = plan_tile_grid_swizzled(p);
         if (!(gram ? edm_gram(p, a, s) : edm_f32(p, a, s))) return fail(TRI_E_UNSUPPORTED, "tri_edm: tile");
         TRI_HIP(hipGetLastError());
         return TRI_OK;

@@ -82,7 +82,7 @@ def test_edm_fp32_padded_rows(tile):
 @pytest.mark.parametrize("data", ["uniform", "clusters", "far off", "outliers", "tiny", "huge",
                                   "wild"])
 def test_edm_fp32_matrix_cores(tile, data):
-    """FP32 mode around the dimensions from which it takes products (64), at
+    """FP32 mode around the dimensions from which it takes products (32), at
     ragged dimensions, pitches and sides, against the exact distances of the
     FP32 coordinates.  A pair is held to the direct sum's bound or, with d^2
     at least 3/8 of the norms' sum S and an error of (d/8 + 4) U S from each
@@ -92,7 +92,8 @@ def test_edm_fp32_matrix_cores(tile, data):
     import torch
     tm = _tm()
     rng = np.random.default_rng(7)
-    for n, d, pad in ((2, 64, 0), (64, 63, 0), (65, 64, 1), (129, 65, 0), (130, 79, 3),
+    for n, d, pad in ((2, 64, 0), (64, 31, 0), (65, 32, 1), (129, 33, 0), (130, 79, 3),
+                      (300, 50, 0), (150, 5, 0),
                       (257, 80, 0), (300, 95, 2), (321, 130, 0), (200, 513, 0)):
         X, _ = inputs.points(n, d, dup_frac=0.02, seed=4700 + n + d)
         if data == "clusters":
