@@ -22,6 +22,7 @@
 
 #include "bodies.hpp"
 #include "common.hpp"
+#include "life_window.hpp"
 #include "maps.hpp"
 
 struct tri_batch;
@@ -59,8 +60,6 @@ struct BatchStepArgs {
 };
 
 constexpr int kBatchThreads = 256;
-// generations per node of the bit-sliced Life body in the batch (its halo)
-constexpr int kBatchBitsGen = kLifeBitsStencilGen;
 constexpr int kPrefixLds = 1024;  // prefix entries kept in LDS (else searched in memory)
 
 template <int TL>
@@ -71,13 +70,8 @@ struct BatchLds {
     static constexpr int EDM_BYTES = EdmF32Shape<TE>::LDS_FLOATS * 4;
     static constexpr int LIFE_BYTES = LifeShape<TL, kBatchThreads>::LDS_WORDS * 4;
     static constexpr int MULTI_BYTES = life_multi_bytes<TL>();
-    // 64 x 64 Life tiles with several generations: one bit-sliced window of
-    // two tiles per wave
-    static constexpr int BITS_BYTES =
-        TL == 64 ? kBatchThreads / 64 * LifeBits16Pair::WORDS * 4 : 0;
     static constexpr int B1 = EDM_BYTES > LIFE_BYTES ? EDM_BYTES : LIFE_BYTES;
-    static constexpr int B2 = B1 > MULTI_BYTES ? B1 : MULTI_BYTES;
-    static constexpr int BYTES = B2 > BITS_BYTES ? B2 : BITS_BYTES;
+    static constexpr int BYTES = B1 > MULTI_BYTES ? B1 : MULTI_BYTES;
 };
 
 // Items are taken kChunk at a time (one atomic per chunk) and the next
@@ -168,122 +162,108 @@ __global__ void __launch_bounds__(kBatchThreads, 4) k_batch_step(BatchStepArgs a
     }
 }
 
-// 64 x 64 Life tiles, every Life grid of the batch with 16-byte rows, and
-// nodes of several generations (temporal plans): items are taken
-// kChunkBits at a time.  The workgroup first runs the chunk's distance
-// items one after the other, then each wave takes two consecutive items,
-// 2 w and 2 w + 1, through the bit-sliced window of two tiles: as one
-// window when they are neighbours in a tile row of one instance (as
-// consecutive lambda blocks mostly are), else each in a window of its own
-// with the second half not written back.  One call site per body keeps the
-// registers at those of the larger body.  VEC4: every distance instance
-// stages its coordinates as 16-byte vectors (chosen at bind time, so that
-// the kernel holds one distance body).
-constexpr int kChunkBits = 2 * kBatchThreads / 64;
+// Temporal plans with Life tile 64, every Life grid with 16-byte rows: the Life
+// items are windows of 256 x 256 cells in the workgroup's registers
+// (life_window_body) that advance up to 32 generations a node, in the window
+// tiling of their grid: sides of h cells, G of a tile row per window, chosen for
+// the longest node.  A node's queue is numbered in claims: first one claim per
+// window (they last longest), then, at the first node, one claim per kChunk
+// distance tiles, whose small items fill the end.  VEC4: every distance
+// instance stages its coordinates as 16-byte vectors (chosen at bind time, so
+// that the kernel holds one distance body).
+//
+// Both halves are bound by vector issue.  512 instances, n log-uniform in [64,
+// 8192], half of them Life for 20 generations in two nodes: the second node 930
+// -> 630 us against windows of two 64 x 64 tiles per wave in LDS; 100 instances
+// up to n = 1024, 19 generations in one node instead of three, d = 3: 181 -> 54
+// us in all.
+struct BatchWindowArgs {
+    const BatchDesc *desc;
+    const int64_t *life, *edm;      // item prefixes of the Life and distance instances
+    const int32_t *life_of, *edm_of;  // their instances
+    int32_t lives, edms;            // how many
+    int32_t step, gens;
+    int32_t h, G, px;               // the window tiling
+    uint32_t windows, claims;       // Life items; all claims of this node
+    uint32_t *head;
+};
+
+using BatchWindow = LifeWindow<4, 4, kBatchThreads / 64>;
 
 template <int TE, bool VEC4>
-__global__ void __launch_bounds__(kBatchThreads, 4) k_batch_step_bits(BatchStepArgs a)
+__global__ void __launch_bounds__(kBatchThreads, 4) k_batch_windows(BatchWindowArgs a)
 {
     constexpr int EDM_BYTES = EdmF32Shape<TE>::LDS_FLOATS * 4;
-    constexpr int PAIR_BYTES = kBatchThreads / 64 * LifeBits16Pair::WORDS * 4;
-    static_assert(kBatchBitsGen == LifeBits16Pair::K, "halo of the paired window");
+    constexpr int LIFE_BYTES = BatchWindow::WORDS * 4;
     __shared__ __attribute__((aligned(16)))
-    unsigned char body_lds[EDM_BYTES > PAIR_BYTES ? EDM_BYTES : PAIR_BYTES];
+    unsigned char body_lds[EDM_BYTES > LIFE_BYTES ? EDM_BYTES : LIFE_BYTES];
     __shared__ int64_t pfx[kPrefixLds];
-    __shared__ int64_t slot;
+    __shared__ uint32_t slot;
 
-    const bool in_lds = a.count + 1 <= kPrefixLds;
-    if (in_lds)
-        for (int k = threadIdx.x; k <= a.count; k += kBatchThreads) pfx[k] = a.prefix[k];
-    uint32_t next = 0;  // thread 0: first item of the chunk claimed ahead
-    if (threadIdx.x == 0) next = atomicAdd(a.head, (uint32_t)kChunkBits);
+    const bool in_lds = a.lives + a.edms + 2 <= kPrefixLds;
+    if (in_lds) {
+        if (a.windows)
+            for (int k = threadIdx.x; k <= a.lives; k += kBatchThreads) pfx[k] = a.life[k];
+        for (int k = threadIdx.x; k <= a.edms; k += kBatchThreads) pfx[a.lives + 1 + k] = a.edm[k];
+    }
+    uint32_t next = 0;  // thread 0: the claim taken ahead
+    if (threadIdx.x == 0) next = atomicAdd(a.head, 1u);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    uint32_t *wl = (uint32_t *)body_lds + wv * LifeBits16Pair::WORDS;
 
-    // the instance of item g (wave-uniform): the largest q with prefix[q] <= g
-    const auto locate = [&](int64_t g, int64_t &lo_g, int64_t &hi_g, BatchDesc &D) {
-        int lo = 0, hi = a.count;
+    // the instance of item g in a prefix of `count` instances (uniform over
+    // the workgroup): the largest q with prefix[q] <= g
+    const auto locate = [&](const int64_t *lds, const int64_t *mem, const int32_t *of, int count,
+                            int64_t g, int64_t &lo_g, int64_t &hi_g, BatchDesc &D) {
+        int lo = 0, hi = count;
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            const int64_t pm = in_lds ? pfx[mid] : a.prefix[mid];
+            const int64_t pm = in_lds ? lds[mid] : mem[mid];
             if (pm <= g) lo = mid;
             else hi = mid;
         }
         lo = __builtin_amdgcn_readfirstlane(lo);
-        lo_g = uniform64(in_lds ? pfx[lo] : a.prefix[lo]);
-        hi_g = uniform64(in_lds ? pfx[lo + 1] : a.prefix[lo + 1]);
-        D = a.desc[a.idx ? __builtin_amdgcn_readfirstlane(a.idx[lo]) : lo];
+        lo_g = uniform64(in_lds ? lds[lo] : mem[lo]);
+        hi_g = uniform64(in_lds ? lds[lo + 1] : mem[lo + 1]);
+        D = a.desc[__builtin_amdgcn_readfirstlane(of[lo])];
     };
-    int64_t lo_g = 0, hi_g = 0;  // item range of the cached instance
-    BatchDesc D{};
     for (;;) {
-        __syncthreads();  // the previous chunk is done with the LDS and with slot
+        __syncthreads();  // the claim before this one is done with the LDS and with slot
         if (threadIdx.x == 0) {
-            slot = (int64_t)next;
-            if ((int64_t)next < a.total) next = atomicAdd(a.head, (uint32_t)kChunkBits);
+            slot = next;
+            if (next < a.claims) next = atomicAdd(a.head, 1u);
         }
         __syncthreads();
-        const int64_t g0 = uniform64(slot);
-        if (g0 >= a.total) return;  // uniform over the workgroup
-        // the chunk's distance items, the whole workgroup each
-        bool used = false;
-        for (int c = 0; c < kChunkBits; ++c) {
+        const uint32_t claim = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+        if (claim >= a.claims) return;  // uniform over the workgroup
+        int64_t lo_g = 0, hi_g = 0;
+        BatchDesc D{};
+        if (claim < a.windows) {
+            locate(pfx, a.life, a.life_of, a.lives, claim, lo_g, hi_g, D);
+            const bool even = (a.step & 1) == 0;
+            const LifeTile t{D.n, D.ld, (const uint8_t *)(even ? D.a : D.b),
+                             (uint8_t *)(even ? D.b : D.a)};
+            int32_t bi, bj;
+            lambda_tile_32(strip_align_first((uint32_t)(claim - lo_g), (uint32_t)a.G), bi, bj);
+            bi = __builtin_amdgcn_readfirstlane(bi);
+            bj = __builtin_amdgcn_readfirstlane(bj);
+            life_window_body<4, 4, kBatchThreads / 64>(t, bi * a.h, bj * a.h, a.h, a.G * a.h, a.px,
+                                                       a.gens, wv, (uint32_t *)body_lds);
+            continue;
+        }
+        const int64_t *const pe = pfx + a.lives + 1;
+        const int64_t total = uniform64(in_lds ? pe[a.edms] : a.edm[a.edms]);
+        const int64_t g0 = (int64_t)(claim - a.windows) * kChunk;
+        for (int c = 0; c < kChunk; ++c) {
             const int64_t g = g0 + c;
-            if (g >= a.total) break;
-            if (g < lo_g || g >= hi_g) locate(g, lo_g, hi_g, D);
-            if (D.kind != TRI_KIND_EDM) continue;
-            if (used) __syncthreads();  // LDS reuse between items
-            used = true;
+            if (g >= total) break;
+            if (g < lo_g || g >= hi_g) locate(pe, a.edm, a.edm_of, a.edms, g, lo_g, hi_g, D);
+            if (c > 0) __syncthreads();  // LDS reuse between items
             int32_t bi, bj;
             lambda_tile((uint64_t)(g - lo_g), 0u, bi, bj);
             bi = __builtin_amdgcn_readfirstlane(bi);
             bj = __builtin_amdgcn_readfirstlane(bj);
             const EdmTile t{D.n, D.d, D.ld, (const float *)D.a, (float *)D.b};
             edm_f32_tile_body<TE, VEC4 ? kEdmStageVec4 : kEdmStageLoop>(t, bi, bj, (float *)body_lds);
-        }
-        if (used) __syncthreads();  // the windows below reuse the LDS
-        // the chunk's Life items: wave w takes items 2 w and 2 w + 1
-        bool life[2];
-        int32_t ti[2], tj[2];
-        int64_t tl[2];
-        BatchDesc TD[2];
-        int64_t l0 = 0, h0 = 0;  // the instance range of item 2 w
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int64_t g = g0 + 2 * wv + e;
-            life[e] = false;
-            ti[e] = tj[e] = 0;
-            tl[e] = -1;
-            if (g < a.total) {
-                int64_t l, h;
-                if (e == 1 && g < h0) {  // in the instance of item 2 w (g - 1 < total, so l0 is set)
-                    l = l0;
-                    TD[1] = TD[0];
-                } else {
-                    locate(g, l, h, TD[e]);
-                    if (e == 0) {
-                        l0 = l;
-                        h0 = h;
-                    }
-                }
-                if (TD[e].kind == TRI_KIND_LIFE) {
-                    life[e] = true;
-                    tl[e] = l;
-                    lambda_tile((uint64_t)(g - l), 0u, ti[e], tj[e]);
-                    ti[e] = __builtin_amdgcn_readfirstlane(ti[e]);
-                    tj[e] = __builtin_amdgcn_readfirstlane(tj[e]);
-                }
-            }
-        }
-        const bool pair = life[0] && life[1] && tl[0] == tl[1] && ti[1] == ti[0] && tj[1] == tj[0] + 1;
-        const int nw = pair ? 1 : (int)life[0] + (int)life[1];
-        const bool even = (a.step & 1) == 0;
-        for (int u = 0; u < nw; ++u) {
-            const int e = (u == 0 && life[0]) ? 0 : 1;
-            const BatchDesc &W = TD[e];
-            const LifeTile t{W.n, W.ld, (const uint8_t *)(even ? W.a : W.b),
-                             (uint8_t *)(even ? W.b : W.a)};
-            life_bits16_pair_body(t, ti[e], tj[e], pair, a.gens, wl);
         }
     }
 }
@@ -294,30 +274,37 @@ __global__ void k_batch_reset(uint32_t *heads, int32_t count)
 }
 
 typedef void (*StepKernel)(BatchStepArgs);
+typedef void (*WindowKernel)(BatchWindowArgs);
 
 template <int TE>
-static StepKernel step_kernel_te(int tl, bool bits, bool vec4)
+static StepKernel step_kernel_te(int tl)
 {
     switch (tl) {
     case 8: return k_batch_step<TE, 8>;
     case 16: return k_batch_step<TE, 16>;
     case 32: return k_batch_step<TE, 32>;
-    case 64:
-        if (!bits) return k_batch_step<TE, 64>;
-        return vec4 ? k_batch_step_bits<TE, true> : k_batch_step_bits<TE, false>;
+    case 64: return k_batch_step<TE, 64>;
     }
     return nullptr;
 }
 
-// bits: the bit-sliced variant (tile 64 only; null otherwise), vec4: its
-// form for batches whose distance instances all stage 16-byte vectors
-static StepKernel step_kernel(int te, int tl, bool bits = false, bool vec4 = false)
+static StepKernel step_kernel(int te, int tl)
 {
-    if (bits && tl != 64) return nullptr;
     switch (te) {
-    case 16: return step_kernel_te<16>(tl, bits, vec4);
-    case 32: return step_kernel_te<32>(tl, bits, vec4);
-    case 64: return step_kernel_te<64>(tl, bits, vec4);
+    case 16: return step_kernel_te<16>(tl);
+    case 32: return step_kernel_te<32>(tl);
+    case 64: return step_kernel_te<64>(tl);
+    }
+    return nullptr;
+}
+
+// vec4: the form for batches whose distance instances all stage 16-byte vectors
+static WindowKernel window_kernel(int te, bool vec4)
+{
+    switch (te) {
+    case 16: return vec4 ? k_batch_windows<16, true> : k_batch_windows<16, false>;
+    case 32: return vec4 ? k_batch_windows<32, true> : k_batch_windows<32, false>;
+    case 64: return vec4 ? k_batch_windows<64, true> : k_batch_windows<64, false>;
     }
     return nullptr;
 }
@@ -338,14 +325,18 @@ struct tri_batch {
     std::vector<BatchDesc> desc;        // host copy (per-instance mode)
     int device = 0;
     uint32_t grid = 0;                  // persistent workgroups
-    StepKernel kernel = nullptr;        // the kernel bound (one of the two below)
-    StepKernel kernel_bytes = nullptr;  // Life tiles byte-sliced
-    StepKernel kernel_bits = nullptr;   // 64 x 64 Life tiles bit-sliced (or null)
-    uint32_t grid_bytes = 0, grid_bits = 0;
+    StepKernel kernel = nullptr;        // tiles
+    WindowKernel windows = nullptr;     // Life windows, if bound to them
+    uint32_t grid_tiles = 0, grid_windows = 0;
+    std::vector<int> window_sched;      // Life generations per node with windows
+    LifeWindowTiles window{};
+    std::vector<int64_t> prefix_life, prefix_edm;  // windows, distance tiles
+    std::vector<int32_t> idx_edm;       // distance instances (Life: idx1)
     // device memory owned by the plan
     BatchDesc *d_desc = nullptr;
     int64_t *d_prefix0 = nullptr, *d_prefix1 = nullptr;
-    int32_t *d_idx1 = nullptr;
+    int64_t *d_prefix_life = nullptr, *d_prefix_edm = nullptr;
+    int32_t *d_idx1 = nullptr, *d_idx_edm = nullptr;
     uint32_t *d_heads = nullptr;
     bool bound = false;
     hipGraph_t graph = nullptr;
@@ -360,7 +351,10 @@ static void batch_free(tri_batch *b)
     (void)hipFree(b->d_desc);
     (void)hipFree(b->d_prefix0);
     (void)hipFree(b->d_prefix1);
+    (void)hipFree(b->d_prefix_life);
+    (void)hipFree(b->d_prefix_edm);
     (void)hipFree(b->d_idx1);
+    (void)hipFree(b->d_idx_edm);
     (void)hipFree(b->d_heads);
     delete b;
 }
@@ -391,6 +385,28 @@ static BatchStepArgs step_args(const tri_batch *b, int s)
     return a;
 }
 
+static BatchWindowArgs window_args(const tri_batch *b, int s)
+{
+    BatchWindowArgs a{};
+    a.desc = b->d_desc;
+    a.life = b->d_prefix_life;
+    a.edm = b->d_prefix_edm;
+    a.life_of = b->d_idx1;
+    a.edm_of = b->d_idx_edm;
+    a.lives = (int32_t)b->idx1.size();
+    a.edms = s == 0 ? (int32_t)b->idx_edm.size() : 0;
+    a.step = s;
+    a.gens = s < (int)b->sched.size() ? b->sched[s] : 0;
+    a.h = b->window.h;
+    a.G = b->window.G;
+    a.px = b->window.px;
+    a.windows = a.gens > 0 ? (uint32_t)b->prefix_life.back() : 0u;
+    const int64_t tiles = s == 0 ? b->prefix_edm.back() : 0;
+    a.claims = a.windows + (uint32_t)((tiles + kChunk - 1) / kChunk);
+    a.head = b->d_heads + s;
+    return a;
+}
+
 // the persistent launches: counter reset, then one kernel per generation
 static tri_status batch_enqueue(const tri_batch *b, hipStream_t s)
 {
@@ -398,9 +414,15 @@ static tri_status batch_enqueue(const tri_batch *b, hipStream_t s)
     k_batch_reset<<<1, 256, 0, s>>>(b->d_heads, S);
     TRI_HIP(hipGetLastError());
     for (int k = 0; k < S; ++k) {
-        BatchStepArgs a = step_args(b, k);
-        if (a.total == 0) continue;
-        hipLaunchKernelGGL(b->kernel, dim3(b->grid), dim3(kBatchThreads), 0, s, a);
+        if (b->windows) {
+            BatchWindowArgs a = window_args(b, k);
+            if (a.claims == 0) continue;
+            hipLaunchKernelGGL(b->windows, dim3(b->grid), dim3(kBatchThreads), 0, s, a);
+        } else {
+            BatchStepArgs a = step_args(b, k);
+            if (a.total == 0) continue;
+            hipLaunchKernelGGL(b->kernel, dim3(b->grid), dim3(kBatchThreads), 0, s, a);
+        }
         TRI_HIP(hipGetLastError());
     }
     return TRI_OK;
@@ -425,11 +447,14 @@ static tri_status batch_build_graph(tri_batch *b)
         TRI_HIP(hipGraphAddKernelNode(&prev, b->graph, nullptr, 0, &np));
     }
     for (int k = 0; k < S; ++k) {
-        BatchStepArgs a = step_args(b, k);
-        if (a.total == 0) continue;
+        BatchStepArgs a{};
+        BatchWindowArgs wa{};
+        if (b->windows) wa = window_args(b, k);
+        else a = step_args(b, k);
+        if (b->windows ? wa.claims == 0 : a.total == 0) continue;
         hipKernelNodeParams np{};
-        void *args[] = {&a};
-        np.func = (void *)b->kernel;
+        void *args[] = {b->windows ? (void *)&wa : (void *)&a};
+        np.func = b->windows ? (void *)b->windows : (void *)b->kernel;
         np.gridDim = dim3(b->grid);
         np.blockDim = dim3(kBatchThreads);
         np.sharedMemBytes = 0;
@@ -473,8 +498,14 @@ tri_status tri_batch_plan(tri_batch **out, int32_t count, const int32_t *host_ki
     b->steps = life_steps;
     b->temporal = (flags & TRI_FLAG_LIFE_TEMPORAL) != 0;
     if (b->temporal && life_steps > 0) b->sched = life_multi_schedule(life_steps, kLifeMaxGen);
-    b->kernel = b->kernel_bytes = step_kernel(edm_tile, life_tile);
-    b->kernel_bits = step_kernel(edm_tile, life_tile, true);
+    b->kernel = step_kernel(edm_tile, life_tile);
+    const bool windows = b->temporal && life_tile == 64;  // at some binding
+    if (windows && life_steps > 0) {
+        b->window_sched = life_multi_schedule(life_steps, kLifeWindowGen);
+        b->window = life_window_tiles<4, 4, kBatchThreads / 64>(b->window_sched[0]);
+        b->prefix_life.push_back(0);
+    }
+    if (windows) b->prefix_edm.push_back(0);
     b->prefix0.push_back(0);
     b->prefix1.push_back(0);
     for (int32_t k = 0; k < count; ++k) {
@@ -506,6 +537,15 @@ tri_status tri_batch_plan(tri_batch **out, int32_t count, const int32_t *host_ki
         if (kd == TRI_KIND_LIFE) {
             b->prefix1.push_back(b->prefix1.back() + T);
             b->idx1.push_back(k);
+            if (!b->prefix_life.empty()) {
+                const int64_t mw = (nk + b->window.h - 1) / b->window.h;
+                b->prefix_life.push_back(b->prefix_life.back() +
+                                         (int64_t)strip_align_prefix((uint32_t)mw,
+                                                                     (uint32_t)b->window.G));
+            }
+        } else if (windows) {
+            b->prefix_edm.push_back(b->prefix_edm.back() + T);
+            b->idx_edm.push_back(k);
         }
     }
     if (b->prefix0.back() >= (1ll << 31)) {
@@ -514,28 +554,32 @@ tri_status tri_batch_plan(tri_batch **out, int32_t count, const int32_t *host_ki
     }
 
     hipError_t e = hipGetDevice(&b->device);
-    int cus = 0, per_cu = 0, per_cu_bits = 0;
+    int cus = 0, per_cu = 0, per_cu_windows = 0;
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);
     if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)b->kernel_bytes,
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)b->kernel,
                                                          kBatchThreads, 0);
-    if (e == hipSuccess && b->kernel_bits)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_bits, (const void *)b->kernel_bits,
-                                                         kBatchThreads, 0);
+    if (e == hipSuccess && windows)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu_windows, (const void *)window_kernel(edm_tile, true), kBatchThreads, 0);
     if (e != hipSuccess) {
         batch_free(b);
         return hip_fail(e, "tri_batch_plan: device query");
     }
-    b->grid = b->grid_bytes = (uint32_t)std::max(1, cus * std::max(1, per_cu));
-    b->grid_bits = (uint32_t)std::max(1, cus * std::max(1, per_cu_bits));
+    b->grid = b->grid_tiles = (uint32_t)std::max(1, cus * std::max(1, per_cu));
+    b->grid_windows = (uint32_t)std::max(1, cus * std::max(1, per_cu_windows));
 
-    const size_t nl = b->idx1.size();
+    const size_t nl = b->idx1.size(), ne = b->idx_edm.size();
+    const size_t pl = b->prefix_life.size(), pe = b->prefix_edm.size();
     const int S = batch_nodes(b);
     e = hipMalloc(&b->d_desc, sizeof(BatchDesc) * count);
     if (e == hipSuccess) e = hipMalloc(&b->d_prefix0, sizeof(int64_t) * (count + 1));
     if (e == hipSuccess) e = hipMalloc(&b->d_prefix1, sizeof(int64_t) * (nl + 1));
     if (e == hipSuccess && nl) e = hipMalloc(&b->d_idx1, sizeof(int32_t) * nl);
     if (e == hipSuccess) e = hipMalloc(&b->d_heads, sizeof(uint32_t) * S);
+    if (e == hipSuccess && pl) e = hipMalloc(&b->d_prefix_life, sizeof(int64_t) * pl);
+    if (e == hipSuccess && pe) e = hipMalloc(&b->d_prefix_edm, sizeof(int64_t) * pe);
+    if (e == hipSuccess && ne) e = hipMalloc(&b->d_idx_edm, sizeof(int32_t) * ne);
     if (e == hipSuccess)
         e = hipMemcpy(b->d_prefix0, b->prefix0.data(), sizeof(int64_t) * (count + 1),
                       hipMemcpyHostToDevice);
@@ -544,6 +588,14 @@ tri_status tri_batch_plan(tri_batch **out, int32_t count, const int32_t *host_ki
                       hipMemcpyHostToDevice);
     if (e == hipSuccess && nl)
         e = hipMemcpy(b->d_idx1, b->idx1.data(), sizeof(int32_t) * nl, hipMemcpyHostToDevice);
+    if (e == hipSuccess && pl)
+        e = hipMemcpy(b->d_prefix_life, b->prefix_life.data(), sizeof(int64_t) * pl,
+                      hipMemcpyHostToDevice);
+    if (e == hipSuccess && pe)
+        e = hipMemcpy(b->d_prefix_edm, b->prefix_edm.data(), sizeof(int64_t) * pe,
+                      hipMemcpyHostToDevice);
+    if (e == hipSuccess && ne)
+        e = hipMemcpy(b->d_idx_edm, b->idx_edm.data(), sizeof(int32_t) * ne, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         batch_free(b);
         return hip_fail(e, "tri_batch_plan: device allocation");
@@ -587,23 +639,22 @@ tri_status tri_batch_bind(tri_batch *b, void *const *host_a, void *const *host_b
     TRI_HIP(hipMemcpy(b->d_desc, desc.data(), sizeof(BatchDesc) * b->count,
                       hipMemcpyHostToDevice));
     b->desc = desc;
-    // the bit-sliced kernel when every Life grid has 16-byte rows and the
-    // nodes advance several generations
-    bool bits = b->kernel_bits != nullptr && b->temporal;
+    // windows when every Life grid has 16-byte rows and the nodes advance
+    // several generations (their lane offsets need pitches up to 2^24)
+    bool windows = b->temporal && b->life_tile == 64;
     bool vec4 = true;  // every distance instance stages 16-byte vectors
     for (const BatchDesc &D : desc) {
-        if (D.kind == TRI_KIND_LIFE && !(D.pad & kDescVec16)) bits = false;
+        if (D.kind == TRI_KIND_LIFE && (!(D.pad & kDescVec16) || D.ld > (1 << 24))) windows = false;
         if (D.kind == TRI_KIND_EDM && !(D.pad & kDescEdmVec4)) vec4 = false;
     }
-    // (the two forms of the bit-sliced kernel have the same launch bound and
-    // LDS, so the same persistent grid)
-    b->kernel = bits ? (vec4 ? step_kernel(b->edm_tile, b->life_tile, true, true) : b->kernel_bits)
-                     : b->kernel_bytes;
-    b->grid = bits ? b->grid_bits : b->grid_bytes;
-    // the bit-sliced kernel advances up to kBatchBitsGen generations per
-    // node (fewer nodes than the plan's schedule, whose counters it reuses)
+    // (the two forms of the window kernel have the same launch bound and LDS,
+    // so the same persistent grid)
+    b->windows = windows ? window_kernel(b->edm_tile, vec4) : nullptr;
+    b->grid = windows ? b->grid_windows : b->grid_tiles;
+    // windows advance more generations per node (fewer nodes than the plan's
+    // schedule, whose counters they reuse)
     if (b->temporal && b->steps > 0)
-        b->sched = life_multi_schedule(b->steps, bits ? kBatchBitsGen : kLifeMaxGen);
+        b->sched = windows ? b->window_sched : life_multi_schedule(b->steps, kLifeMaxGen);
     if (b->exec) { (void)hipGraphExecDestroy(b->exec); b->exec = nullptr; }
     if (b->graph) { (void)hipGraphDestroy(b->graph); b->graph = nullptr; }
     tri_status st = batch_build_graph(b);

@@ -334,4 +334,31 @@ __device__ __forceinline__ void life_window_body(const LifeTile &p, int32_t i0, 
         life_window_run<LX, RR, NW, true>(p, i0, j0, h, w, px, gens, wv, lds);
 }
 
+// Generations of one launch at most (on small grids the stencil takes more).
+constexpr int kLifeWindowGen = 32;
+
+// The tiling a window yields after `gens` generations: the largest G tiles of
+// side h, in windows that start at multiples of 16 cells, px cells left of
+// the tiles.
+struct LifeWindowTiles {
+    int32_t h, G, px;
+};
+
+template <int LX, int RR, int NW>
+inline LifeWindowTiles life_window_tiles(int gens)
+{
+    using S = LifeWindow<LX, RR, NW>;
+    LifeWindowTiles t{0, 0, (gens + 15) / 16 * 16};
+    for (int32_t g = 1; g <= 4; ++g) {
+        const int32_t step = g == 4 ? 4 : (g == 2 ? 8 : 16);
+        const int32_t rows = S::H - 2 * gens, cols = (S::W - t.px - gens) / g;
+        const int32_t side = (rows < cols ? rows : cols) / step * step;
+        if ((int64_t)g * side * side > (int64_t)t.G * t.h * t.h) {
+            t.G = g;
+            t.h = side;
+        }
+    }
+    return t;
+}
+
 }  // namespace trimap

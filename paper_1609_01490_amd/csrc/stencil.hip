@@ -195,19 +195,8 @@ __global__ void __launch_bounds__(64 * NW) k_life_window(LifeTile t, int gens, i
 template <int LX, int RR, int NW>
 static void life_window_launch_shape(const LifeTile &t, int gens, hipStream_t s)
 {
-    using S = LifeWindow<LX, RR, NW>;
-    // the largest G tiles of side h that the window yields after `gens`
-    // generations, with windows that start at multiples of 16 cells
-    const int px = (gens + 15) / 16 * 16;
-    int32_t G = 0, h = 0;
-    for (int32_t g = 1; g <= 4; ++g) {
-        const int32_t step = g == 4 ? 4 : (g == 2 ? 8 : 16);
-        const int32_t side = std::min(S::H - 2 * gens, (S::W - px - gens) / g) / step * step;
-        if ((int64_t)g * side * side > (int64_t)G * h * h) {
-            G = g;
-            h = side;
-        }
-    }
+    const LifeWindowTiles w = life_window_tiles<LX, RR, NW>(gens);
+    const int32_t h = w.h, G = w.G, px = w.px;
     const uint32_t m = (uint32_t)((t.n + h - 1) / h);
     const uint32_t windows = (uint32_t)strip_align_prefix(m, (uint32_t)G);
     k_life_window<LX, RR, NW><<<windows, 64 * NW, 0, s>>>(t, gens, h, G, px);
@@ -217,7 +206,7 @@ static void life_window_launch_shape(const LifeTile &t, int gens, hipStream_t s)
 // 256 cells, and cost as much as any halo above 16; on the smallest grids a
 // launch costs more than the cells that a 50-cell halo computes twice (n =
 // 1000, 100 generations: 4 launches of 25 50 us, 2 of 50 39 us; n = 2000 56, 62).
-static int life_window_gens(int64_t n) { return n <= 1536 ? 50 : 32; }
+static int life_window_gens(int64_t n) { return n <= 1536 ? 50 : kLifeWindowGen; }
 
 // Grids the windows take: a pitch of at least one 16-cell chunk, and lane
 // offsets (up to 255 rows) below 2^32.
@@ -380,7 +369,7 @@ bool launch_life_multi_lambda(int tile, const TileGrid &g, const LifeTile &t, in
     else { gx = 1u << 16; gy = (uint32_t)((g.T + gx - 1) / gx); }
     const dim3 grid(gx, gy);
     if (gens > kLifeMaxGen && tile != 64) return false;
-    if (gens > kLifeBitsStencilGen) return false;
+    if (gens > kLifeWindowGen) return false;
     switch (tile) {
     case 16: k_life_multi<MAP_LAMBDA, 16><<<grid, 256, 0, s>>>(a, gens); return true;
     case 32: k_life_multi<MAP_LAMBDA, 32><<<grid, 256, 0, s>>>(a, gens); return true;
