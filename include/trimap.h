@@ -334,7 +334,7 @@ tri_status tri_collide(const tri_plan *plan, const float *spheres, int dim, int3
  * Batched uneven domains in one persistent launch per generation.
  *
  * Instance k (0 <= k < count) is a distance map (TRI_KIND_EDM: strict lower
- * triangle of n_k points in d_k dimensions, FP32 direct arithmetic, edm_tile
+ * triangle of n_k points in d_k dimensions, arithmetic of TRI_EDM_FP32, edm_tile
  * in {16, 32, 64}) or a Game of Life (TRI_KIND_LIFE: lower triangle of side
  * n_k, life_tile in {8, 16, 32, 64}, life_steps generations).  Each instance
  * contributes m_k (m_k + 1) / 2 tiles (Section 3.1); a global work item g is
@@ -389,8 +389,9 @@ tri_status tri_batch_plan(tri_batch **out, int32_t count, const int32_t *host_ki
  * generations the Life result is in a[k], after an odd number in b[k].
  * When the plan has life_tile 64 with TRI_FLAG_LIFE_TEMPORAL and every Life
  * grid has a pitch that is a multiple of 16 and 16-byte aligned buffers,
- * the bound kernel moves Life tiles bit-sliced, one per wave, with 16-byte
- * row loads and stores (same results).  Copies the descriptors to the
+ * the bound kernel advances windows of 256 x 256 cells in registers, up to 32
+ * generations per node (same results).  Distance instances with edm_tile 64
+ * and 32 to 512 dimensions are computed as TRI_EDM_FP32 does there.  Copies the descriptors to the
  * device (synchronously) and builds and instantiates the graph.  Rebinding
  * replaces both. */
 tri_status tri_batch_bind(tri_batch *b, void *const *host_a, void *const *host_b,

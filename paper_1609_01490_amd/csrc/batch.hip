@@ -22,6 +22,7 @@
 
 #include "bodies.hpp"
 #include "common.hpp"
+#include "edm_gram.hpp"
 #include "life_window.hpp"
 #include "maps.hpp"
 
@@ -29,7 +30,8 @@ struct tri_batch;
 
 namespace trimap {
 
-bool launch_edm_f32_lambda(int tile, const TileGrid &g, const EdmTile &t, hipStream_t s);
+bool launch_edm_f32_lambda(int tile, const TileGrid &g, const EdmTile &t, bool gram,
+                           hipStream_t s);
 bool launch_life_lambda(int tile, const TileGrid &g, const LifeTile &t, hipStream_t s);
 bool launch_life_multi_lambda(int tile, const TileGrid &g, const LifeTile &t, int gens,
                               hipStream_t s);
@@ -39,14 +41,15 @@ struct BatchDesc {
     int32_t kind;  // TRI_KIND_*
     int32_t n;
     int32_t d;
-    int32_t pad;   // kDescVec16: a Life grid whose rows move as 16-byte vectors
+    int32_t pad;   // kDesc flags
     int64_t ld;    // distance map: ldx; Life: row pitch in bytes
     void *a;       // distance map: x; Life: grid of even generations
     void *b;       // distance map: out; Life: grid of odd generations
 };
 
-constexpr int32_t kDescVec16 = 1;  // ld % 16 == 0 and 16-byte aligned grids
+constexpr int32_t kDescVec16 = 1;  // Life: ld % 16 == 0 and 16-byte aligned grids
 constexpr int32_t kDescEdmVec4 = 2;  // distance map: coordinates staged as 16-byte vectors
+constexpr int32_t kDescEdmGram = 4;  // distance map: 64 x 64 tiles on the matrix cores
 
 struct BatchStepArgs {
     const BatchDesc *desc;
@@ -62,17 +65,54 @@ struct BatchStepArgs {
 constexpr int kBatchThreads = 256;
 constexpr int kPrefixLds = 1024;  // prefix entries kept in LDS (else searched in memory)
 
+// One distance-map tile: 64 x 64 tiles of 32 to kBatchGramDims dimensions (LDS
+// for the centre) take the products, as the single FP32 map does: 512
+// instances, half of them d = 32 maps, 3145 -> 2670 us.
+constexpr int kBatchGramDims = 512;
+
+struct BatchGram {
+    GramLds<64> tile;
+    __attribute__((aligned(16))) float centre[kBatchGramDims];
+};
+
+template <int TE>
+constexpr int batch_edm_bytes()
+{
+    const int direct = EdmF32Shape<TE>::LDS_FLOATS * 4;
+    return TE == 64 && (int)sizeof(BatchGram) > direct ? (int)sizeof(BatchGram) : direct;
+}
+
 template <int TL>
 constexpr int life_multi_bytes() { return TL >= 16 ? 2 * LifeMultiShape<(TL >= 16 ? TL : 16)>::WORDS * 4 : 0; }
 
 template <int TE, int TL>
 struct BatchLds {
-    static constexpr int EDM_BYTES = EdmF32Shape<TE>::LDS_FLOATS * 4;
+    static constexpr int EDM_BYTES = batch_edm_bytes<TE>();
     static constexpr int LIFE_BYTES = LifeShape<TL, kBatchThreads>::LDS_WORDS * 4;
     static constexpr int MULTI_BYTES = life_multi_bytes<TL>();
     static constexpr int B1 = EDM_BYTES > LIFE_BYTES ? EDM_BYTES : LIFE_BYTES;
     static constexpr int BYTES = B1 > MULTI_BYTES ? B1 : MULTI_BYTES;
 };
+
+template <int TE>
+__device__ __forceinline__ void batch_edm_tile(const BatchDesc &D, int32_t bi, int32_t bj,
+                                               bool vec4, unsigned char *lds)
+{
+    // the lane's number anew for each tile, or what follows from it would be kept
+    // in registers over the whole queue
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const EdmTile t{D.n, D.d, D.ld, (const float *)D.a, (float *)D.b};
+    if constexpr (TE == 64) {
+        if (D.pad & kDescEdmGram) {
+            BatchGram *const g = (BatchGram *)lds;
+            edm_gram_body<64>(t, bi, bj, g->tile, g->centre, tid);
+            return;
+        }
+    }
+    if (vec4) edm_f32_tile_body<TE, kEdmStageVec4>(t, bi, bj, (float *)lds, tid);
+    else edm_f32_tile_body<TE, kEdmStageLoop>(t, bi, bj, (float *)lds, tid);
+}
 
 // Items are taken kChunk at a time (one atomic per chunk) and the next
 // chunk is claimed as soon as the current one starts, so the atomic's
@@ -140,11 +180,7 @@ __global__ void __launch_bounds__(kBatchThreads, 4) k_batch_step(BatchStepArgs a
             bi = __builtin_amdgcn_readfirstlane(bi);
             bj = __builtin_amdgcn_readfirstlane(bj);
             if (D.kind == TRI_KIND_EDM) {
-                const EdmTile t{D.n, D.d, D.ld, (const float *)D.a, (float *)D.b};
-                if (D.pad & kDescEdmVec4)
-                    edm_f32_tile_body<TE, kEdmStageVec4>(t, bi, bj, (float *)body_lds);
-                else
-                    edm_f32_tile_body<TE, kEdmStageLoop>(t, bi, bj, (float *)body_lds);
+                batch_edm_tile<TE>(D, bi, bj, (D.pad & kDescEdmVec4) != 0, body_lds);
             } else {
                 const bool even = (a.step & 1) == 0;
                 const LifeTile t{D.n, D.ld, (const uint8_t *)(even ? D.a : D.b),
@@ -193,7 +229,7 @@ using BatchWindow = LifeWindow<4, 4, kBatchThreads / 64>;
 template <int TE, bool VEC4>
 __global__ void __launch_bounds__(kBatchThreads, 4) k_batch_windows(BatchWindowArgs a)
 {
-    constexpr int EDM_BYTES = EdmF32Shape<TE>::LDS_FLOATS * 4;
+    constexpr int EDM_BYTES = batch_edm_bytes<TE>();
     constexpr int LIFE_BYTES = BatchWindow::WORDS * 4;
     __shared__ __attribute__((aligned(16)))
     unsigned char body_lds[EDM_BYTES > LIFE_BYTES ? EDM_BYTES : LIFE_BYTES];
@@ -246,8 +282,10 @@ __global__ void __launch_bounds__(kBatchThreads, 4) k_batch_windows(BatchWindowA
             lambda_tile_32(strip_align_first((uint32_t)(claim - lo_g), (uint32_t)a.G), bi, bj);
             bi = __builtin_amdgcn_readfirstlane(bi);
             bj = __builtin_amdgcn_readfirstlane(bj);
+            int lane = threadIdx.x & 63;  // (anew, as for the distance tiles)
+            asm volatile("" : "+v"(lane));
             life_window_body<4, 4, kBatchThreads / 64>(t, bi * a.h, bj * a.h, a.h, a.G * a.h, a.px,
-                                                       a.gens, wv, (uint32_t *)body_lds);
+                                                       a.gens, wv, lane, (uint32_t *)body_lds);
             continue;
         }
         const int64_t *const pe = pfx + a.lives + 1;
@@ -262,8 +300,7 @@ __global__ void __launch_bounds__(kBatchThreads, 4) k_batch_windows(BatchWindowA
             lambda_tile((uint64_t)(g - lo_g), 0u, bi, bj);
             bi = __builtin_amdgcn_readfirstlane(bi);
             bj = __builtin_amdgcn_readfirstlane(bj);
-            const EdmTile t{D.n, D.d, D.ld, (const float *)D.a, (float *)D.b};
-            edm_f32_tile_body<TE, VEC4 ? kEdmStageVec4 : kEdmStageLoop>(t, bi, bj, (float *)body_lds);
+            batch_edm_tile<TE>(D, bi, bj, VEC4, body_lds);
         }
     }
 }
@@ -628,7 +665,9 @@ tri_status tri_batch_bind(tri_batch *b, void *const *host_a, void *const *host_b
             // the byte offsets fit 32 bits (as for the single FP32 kernel)
             if (D.d % 4 == 0 && D.ld % 4 == 0 && ((uintptr_t)D.a & 15) == 0 &&
                 (uint64_t)D.n * (uint64_t)D.ld * 4 < (1ull << 31))
-                D.pad = kDescEdmVec4;
+                D.pad |= kDescEdmVec4;
+            if (b->edm_tile == 64 && D.d <= kBatchGramDims && edm_gram_takes(64, D.d, D.ld))
+                D.pad |= kDescEdmGram;
         } else {
             if (D.ld < D.n || D.ld % 4 || (((uintptr_t)D.a | (uintptr_t)D.b) & 3))
                 return fail(TRI_E_INVAL,
@@ -686,7 +725,7 @@ tri_status tri_batch_launch(tri_batch *b, int how, void *stream)
             if (b->tiles[k] == 0) continue;
             if (D.kind == TRI_KIND_EDM) {
                 const EdmTile t{D.n, D.d, D.ld, (const float *)D.a, (float *)D.b};
-                if (!launch_edm_f32_lambda(tile, g, t, s))
+                if (!launch_edm_f32_lambda(tile, g, t, (D.pad & kDescEdmGram) != 0, s))
                     return fail(TRI_E_UNSUPPORTED, "tri_batch_launch: distance instance %d", k);
                 TRI_HIP(hipGetLastError());
             } else {

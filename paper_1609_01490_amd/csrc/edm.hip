@@ -12,7 +12,7 @@
 // reads broadcast / consecutive words.  Bound by the vector ALU (2 VALU ops
 // per pair and dimension).  From 32 dimensions on, at tiles of 64 and 128, the
 // squares come from FP32 norms and a split Gram product that is nearer to the
-// exact distances than the direct sum (k_edm_gram).
+// exact distances than the direct sum (edm_gram_body).
 //
 // TRI_EDM_BF16X3 / TRI_EDM_BF16: d^2 = |x_i|^2 + |x_j|^2 - 2 x_i.x_j with the
 // Gram term on the matrix cores.  A pre-pass centres the points on their mean
@@ -28,6 +28,7 @@
 // The output write (4 B per pair) bounds this path.
 #include "bodies.hpp"
 #include "common.hpp"
+#include "edm_gram.hpp"
 #include "maps.hpp"
 
 #include <mutex>
@@ -91,8 +92,6 @@ static bool edm_f32(const tri_plan *p, const EdmArgs &a, hipStream_t s)
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kEdmTile = 128;     // output tile of the MFMA kernel
 constexpr int kColsumRows = 64;   // rows per block of the column-sum pass
@@ -268,34 +267,6 @@ __device__ __forceinline__ float direct_d2(const float *x, int64_t ldx, int32_t 
     return s;
 }
 
-// The same sum in the same order with the loads of eight dimensions in flight,
-// for kernels that have the registers at that point.
-__device__ __forceinline__ float direct_d2_wide(const float *x, int64_t ldx, int32_t d, int32_t i,
-                                                int32_t j)
-{
-    const float *xi = x + (int64_t)i * ldx, *xj = x + (int64_t)j * ldx;
-    float s = 0.f;
-    int32_t k = 0;
-    for (; k + 8 <= d; k += 8) {
-        float a[8], b[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            a[u] = xi[k + u];
-            b[u] = xj[k + u];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float df = a[u] - b[u];
-            s = __builtin_fmaf(df, df, s);
-        }
-    }
-    for (; k < d; ++k) {
-        const float df = xi[k] - xj[k];
-        s = __builtin_fmaf(df, df, s);
-    }
-    return s;
-}
-
 // LDS staging of the operands: the tile's 128 row points and 128 column
 // points, kKC dimensions at a time, rows padded so that the 16-byte operand
 // reads of eight consecutive rows hit distinct banks.  The next chunk is
@@ -309,16 +280,6 @@ constexpr int kVecPerThread = kEdmTile * kKC / 8 / 256;  // 16-byte vectors per 
 // of this wave are outstanding (vmcnt(n), 0 <= n <= 63), leaving expcnt and
 // lgkmcnt at their maxima (no wait).
 constexpr unsigned waitcnt_vm(unsigned n) { return (n & 0xFu) | ((n >> 4) << 14) | 0x0F70u; }
-
-// Workgroup barrier that orders LDS traffic only: wait for this wave's LDS
-// operations, then s_barrier.  Unlike __syncthreads() it does not wait for
-// outstanding global stores or prefetch loads.  (A global load that feeds
-// LDS is waited for by the data dependency of the LDS store.)
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0), vmcnt and expcnt untouched
-    __builtin_amdgcn_s_barrier();
-}
 
 template <bool SPLIT>
 struct EdmStage {
@@ -562,8 +523,6 @@ __device__ __forceinline__ void edm_distances_to_lds(const EdmMfmaArgs &p, f32x1
 // row.  Row i starts at i (i - 1) / 2, any word, hence the 4-byte aligned
 // vector type.  The output is written once and not read back here:
 // non-temporal stores.
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
 __device__ __forceinline__ void edm_store_tile_rows(const EdmMfmaArgs &p, const float *D,
                                                     int32_t RW, int32_t CW, int w, int l)
 {
@@ -592,358 +551,23 @@ __device__ __forceinline__ void edm_store_tile_rows(const EdmMfmaArgs &p, const 
     }
 }
 
-// ---------------------------------------------------------------------------
-// The FP32 mode on the matrix cores (from kGramMinDims dimensions on, tiles of
-// 64 and 128; no workspace, one launch).
-//
-// d^2 = |y_i|^2 + |y_j|^2 - 2 y_i.y_j with y = sc (x - c): c is the mean of 16
-// of the tile's own points, so that the norms are no larger than the tile's
-// spread, and sc the power of two that brings those points' spread to 2^8.
-// The norms are FP32 sums of the squares of y.  The products take y as two
-// FP16 values, h + l (22 significant bits or more; spreads up to 2^7 times the
-// samples' fit, see the norm test): h.l + l.h + h.h accumulated in FP32 by
-// v_mfma_f32_32x32x16_f16.
-//
-// Error.  Rounding leaves about 2^-24 (|y_i|^2 + |y_j|^2) in d^2, whatever d,
-// while the direct sum's error grows with d.  A pair with d^2 < kGramNear of
-// that sum, or with a sum that is no finite number well inside FP32's range, is
-// recomputed from the differences in the direct body's order, and a tile with
-// many of them is left to the direct body, most of the time after 32 dimensions
-// (ten tight clusters in random order, where every tile is: d = 128 770 -> 1020
-// us, without the early test 1130; a hundred clusters 760 -> 510).  Against 64 bits, uniform points with
-// 1 % near-duplicates, relative L2 and largest relative error, direct / here:
-// 4.6e-8 / 3.9e-8 and 2.4e-7 / 2.6e-7 at d = 24, 5.2e-8 / 3.9e-8 and 2.9e-7 /
-// 2.4e-7 at d = 32, 6.4e-8 / 3.4e-8 and 3.7e-7 / 2.2e-7 at d = 63, 9.2e-8 /
-// 4.0e-8 and 4.8e-7 / 2.6e-7 at d = 128, 1.3e-7 / 3.5e-8 and 6.4e-7 / 2.5e-7 at
-// d = 256; d = 128 in clusters of 0.6 times their centres' spread 9.1e-8 /
-// 4.0e-8 and 4.5e-7 / 3.7e-7.  Hence the line at 32: below it the largest error
-// would be larger than the direct sum's.
-//
-// Work.  The direct form is bound by two vector operations per pair and
-// dimension.  Here they are about 5 per staged coordinate and 10 per pair, and
-// with the products (half as long, on the matrix cores, partly in their shadow)
-// and the power limit's clock they bound the kernel.  n = 16384: d = 128 706 ->
-// 234 us (tile 128) and 770 -> 288 us (tile 64), d = 64 404 -> 172 us; n = 10007,
-// d = 256 515 -> 143 us; n = 2000, d = 128 26.0 -> 11.4 us.  Below d = 64 against
-// the direct form as it is now, tile 64 / 128: n = 16384, d = 32 247 -> 172 /
-// 233 -> 158 us, d = 50 379 -> 201 / 380 -> 174 us; n = 257, d = 32 6.8 -> 6.3 /
-// 16.0 -> 9.0 us; n = 2000, d = 32 9.9 -> 10.1 / 17.4 -> 10.1 us.  Tried in its place,
-// d = 128: FP32 products (v_mfma_f32_32x32x2_f32, which shares the vector
-// units: no overlap) 358 us; three BF16 parts, six products, 288 us.
-//
-// Layout.  16 dimensions at a time, two buffers, one barrier per chunk: a chunk
-// is centred, split and stored while the products of the one before it run.
-// Rows are 32 bytes; the two 16-byte slots of a row are swapped every eight
-// rows, so that the 16-byte reads of 16 rows fall on distinct banks.  Waves have
-// 64 x 32 pairs (tile 64: 32 x 32) and two workgroups share a CU.  The outputs
-// are cached, neighbouring tiles on one XCD: the parts of a line that two waves
-// or two tiles write meet in its L2 (d = 64: 288 -> 172 us; either alone 209 and
-// 267 us).
-// ---------------------------------------------------------------------------
-constexpr int kGramMinDims = 32;
-constexpr float kGramNear = 0.375f;
-constexpr int kGramK = 16;         // dimensions per staged chunk
-constexpr int kGramLaneNear = 4;   // near pairs per lane (of 32 or 16) that a tile may hold
-
-template <int TILE>
-struct GramLds {
-    static constexpr int kPlane = TILE * kGramK * 2;  // bytes
-    static constexpr int kBuffer = kPlane * 4;
-    static constexpr int kDirect = (TILE / 64) * EdmF32Shape<64>::LDS_FLOATS * 4;
-    static constexpr int kBytes = kBuffer * 2 > kDirect ? kBuffer * 2 : kDirect;
-};
-
-// Byte offset in a plane of 16-byte slot q (dimensions 8 q .. 8 q + 7) of a point.
-__device__ __forceinline__ int gram_slot(int point, int q)
-{
-    return point * (kGramK * 2) + 16 * (q ^ ((point >> 3) & 1));
-}
-
-// v = h + l to 22 significant bits or 2^-25, whichever is coarser.
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ void gram_split(const f32x4 &v, f16x4 &h, f16x4 &l)
-{
-    h = __builtin_convertvector(v, f16x4);
-    f32x4 r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = __builtin_fmaf((float)h[e], -1.f, v[e]);
-    l = __builtin_convertvector(r, f16x4);
-}
-
-// v holds coordinates d - 4 .. d - 1: those from d - 4 + sh on, zeros behind.
-__device__ __forceinline__ f32x4 gram_tail(const f32x4 &v, int32_t sh)
-{
-    f32x4 r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        r[e] = 0.f;
-#pragma unroll
-        for (int g = e; g < 4; ++g) r[e] = sh == g - e ? v[g] : r[e];
-    }
-    return r;
-}
-
-template <bool FULL, int WA>
-__device__ __forceinline__ void gram_store(char *ob, const f32x16 (&acc)[WA], int32_t R0,
-                                           int32_t j, int32_t n, int l)
-{
-#pragma unroll
-    for (int a = 0; a < WA; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int32_t i = R0 + 32 * a + 8 * q + 4 * (l >> 5);
-            uint32_t off = (uint32_t)((i - R0) * (i + R0 - 1)) / 2u + (uint32_t)j;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float dd = sqrt_near1(acc[a][4 * q + u]);
-                if (FULL || (i < n && j < i)) *(float *)(ob + (off << 2)) = dd;
-                off += (uint32_t)i;  // start of row i + 1
-                ++i;
-            }
-        }
-}
-
 template <int MAP, int TILE>
 __global__ void __launch_bounds__(4 * TILE, 4) k_edm_gram(EdmArgs p)
 {
-    constexpr int NT = 4 * TILE;
-    constexpr int WA = TILE / 64;          // a wave has WA blocks of 32 rows, 32 columns
-    constexpr int WT = TILE / 2;           // its rows
-    __shared__ __attribute__((aligned(16))) unsigned char lds[GramLds<TILE>::kBytes];
-    __shared__ __attribute__((aligned(16))) float sN[2 * TILE];
-    __shared__ int sMany;
-    __shared__ float sSpread[NT / 64];
-    extern __shared__ __attribute__((aligned(16))) float sC[];  // centre, whole chunks
-
+    __shared__ GramLds<TILE> sh;
+    extern __shared__ __attribute__((aligned(16))) float centre[];
     int32_t bi, bj;
     if (!tile_of_block<MAP>(p.g, bi, bj)) return;
-    const int t = threadIdx.x, l = t & 63;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int32_t n = p.t.n, d = p.t.d;
-    const int64_t ldx = p.t.ldx;
-    const int32_t ri0 = 1 + bi * TILE, cj0 = bj * TILE;
-    const char *const xi = (const char *)(p.t.x + (int64_t)ri0 * ldx);  // ri0, cj0 < n
-    const char *const xj = (const char *)(p.t.x + (int64_t)cj0 * ldx);
-    const uint32_t pitch = (uint32_t)ldx * 4u;
-
-    const int kq = t % 4, pt = t / 4;      // this thread stages dimensions 4 kq .. of point pt
-    const char *const pi = xi + (uint32_t)min(pt, n - 1 - ri0) * pitch;
-    const char *const pj = xj + (uint32_t)min(pt, n - 1 - cj0) * pitch;
-    f32x4 vi, vj;
-    auto load = [&](int32_t k0) {
-        const uint32_t o = (uint32_t)min(k0 + 4 * kq, d - 4) * 4u;
-        vi = *(const f32x4u *)(pi + o);
-        vj = *(const f32x4u *)(pj + o);
-    };
-    load(0);
-
-    if (t == 0) sMany = 0;
-    float spread = 0.f;
-    for (int32_t k = t; k < (d + kGramK - 1) / kGramK * kGramK; k += NT) {
-        float v[16];
-        const uint32_t ko = (uint32_t)min(k, d - 1) * 4u;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            v[u] = *(const float *)(xi + (uint32_t)min(u * (TILE / 8), n - 1 - ri0) * pitch + ko);
-            v[8 + u] = *(const float *)(xj + (uint32_t)min(u * (TILE / 8), n - 1 - cj0) * pitch + ko);
-        }
-        float s = 0.f, lo = v[0], hi = v[0];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            s += v[u];
-            lo = fminf(lo, v[u]);
-            hi = fmaxf(hi, v[u]);
-        }
-        sC[k] = k < d ? s * 0.0625f : 0.f;
-        spread = fmaxf(spread, hi - lo);
-    }
-#pragma unroll
-    for (int h = 1; h < 64; h *= 2) spread = fmaxf(spread, __shfl_xor(spread, h));
-    if (l == 0) sSpread[w] = spread;
-    __syncthreads();
-    // the power of two that brings the samples' spread to about 2^8
-#pragma unroll
-    for (int h = 0; h < NT / 64; ++h) spread = fmaxf(spread, sSpread[h]);
-    const uint32_t ex = __builtin_bit_cast(uint32_t, spread) >> 23;
-    const float sc = ex ? __builtin_bit_cast(float, min(262u - ex, 254u) << 23) : 1.f;
-
-    const int wr = w & 1, wc = w >> 1, lr = l & 31;
-    constexpr int kPlane = GramLds<TILE>::kPlane, kBuffer = GramLds<TILE>::kBuffer;
-    const int so = gram_slot(pt, kq >> 1) + 8 * (kq & 1);
-    float ni[2] = {0.f, 0.f}, nj[2] = {0.f, 0.f};
-    // this thread's vectors of chunk k0, centred and split, into buffer q
-    auto stage = [&](int32_t k0, unsigned char *q) {
-        const int32_t k = k0 + 4 * kq;
-        const f32x4 c = *(const f32x4 *)&sC[k] * sc;
-        if (k0 + kGramK > d) {             // dimensions from d on are zero, as c is there
-            const int32_t sh = k - min(k, d - 4);
-            vi = gram_tail(vi, sh);
-            vj = gram_tail(vj, sh);
-        }
-        f32x4 yi, yj;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            yi[e] = __builtin_fmaf(vi[e], sc, -c[e]);
-            yj[e] = __builtin_fmaf(vj[e], sc, -c[e]);
-            ni[e & 1] = __builtin_fmaf(yi[e], yi[e], ni[e & 1]);
-            nj[e & 1] = __builtin_fmaf(yj[e], yj[e], nj[e & 1]);
-        }
-        f16x4 h, lo;
-        gram_split(yi, h, lo);
-        *(f16x4 *)(q + so) = h;
-        *(f16x4 *)(q + kPlane + so) = lo;
-        gram_split(yj, h, lo);
-        *(f16x4 *)(q + 2 * kPlane + so) = h;
-        *(f16x4 *)(q + 3 * kPlane + so) = lo;
-    };
-    stage(0, lds);
-    if (kGramK < d) load(kGramK);
-    lds_barrier();
-
-    int oa[WA];
-#pragma unroll
-    for (int a = 0; a < WA; ++a) oa[a] = gram_slot(WT * wr + 32 * a + lr, l >> 5);
-    const int ob0 = 2 * kPlane + gram_slot(32 * wc + lr, l >> 5);
-    f32x16 acc[WA];
-#pragma unroll
-    for (int a = 0; a < WA; ++a) acc[a] = f32x16{};
-    // A point's scaled norm so far, from the four threads that stage it.
-    auto norm = [&](const float (&v)[2]) {
-        float s = v[0] + v[1];
-#pragma unroll
-        for (int h = 1; h < 4; h *= 2) s += __shfl_xor(s, h);
-        return s;
-    };
-    const int32_t R0 = ri0 + WT * wr, C0 = cj0 + 32 * wc;
-    const int32_t j = C0 + lr;
-    bool direct = false;                   // the same for the whole workgroup
-    int buf = 0;
-    for (int32_t k0 = 0; k0 < d; k0 += kGramK) {
-        if (k0 == kGramK) {                // of the 32 dimensions staged so far
-            const float mi = norm(ni), mj = norm(nj);
-            if (kq == 0) {
-                sN[pt] = mi;
-                sN[TILE + pt] = mj;
-            }
-        }
-        const unsigned char *const q = lds + buf;
-        buf ^= kBuffer;
-        f16x8 va[2][WA], vb[2];
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            vb[g] = *(const f16x8 *)(q + ob0 + g * kPlane);
-#pragma unroll
-            for (int a = 0; a < WA; ++a) va[g][a] = *(const f16x8 *)(q + oa[a] + g * kPlane);
-        }
-        if (k0 + kGramK < d) {             // the next chunk, and the loads of the one after it
-            stage(k0 + kGramK, lds + buf);
-            if (k0 + 2 * kGramK < d) load(k0 + 2 * kGramK);
-        }
-        // the small products first
-        constexpr int QA[3] = {1, 0, 0}, QB[3] = {0, 1, 0};
-#pragma unroll
-        for (int g = 0; g < 3; ++g)
-#pragma unroll
-            for (int a = 0; a < WA; ++a)
-                acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[QA[g]][a], vb[QB[g]], acc[a],
-                                                                0, 0, 0);
-        lds_barrier();
-        if (k0 == kGramK) {
-            // Four of each lane's pairs over the first 32 dimensions: a tile
-            // whose pairs are often near is left to the direct body here.
-            const f32x4 si = *(const f32x4 *)&sN[WT * wr + 4 * (l >> 5)];
-            const float sj = sN[TILE + 32 * wc + lr];
-            int many = 0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float s = si[u] + sj;
-                many += __popcll(__ballot(!(__builtin_fmaf(-2.f, acc[0][u], s) >= kGramNear * s) &&
-                                          j < R0 + 4 * (l >> 5) + u));
-            }
-            if (l == 0 && many) atomicAdd(&sMany, many);
-            lds_barrier();
-            direct = sMany > NT / 4;       // one in sixteen
-            if (direct) break;
-        }
-    }
-
-    // norms; one out of range (the halves of a point whose scaled norm is below
-    // 2^30 are finite) makes its pairs' sums NaN, and those pairs near
-    const float mi = norm(ni), mj = norm(nj);
-    const float inv2 = 1.f / (sc * sc);
-    if (kq == 0) {
-        sN[pt] = mi < 0x1p30f && mi * inv2 < 0x1p93f ? mi * inv2 : __builtin_nanf("");
-        sN[TILE + pt] = mj < 0x1p30f && mj * inv2 < 0x1p93f ? mj * inv2 : __builtin_nanf("");
-    }
-    __syncthreads();
-
-    const bool work = R0 < n && C0 < R0 + WT - 1;  // some pair j < i < n in the wave's block
-    const float sj = sN[TILE + 32 * wc + lr];
-    bool near = false;
-#pragma unroll
-    for (int a = 0; a < WA; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f32x4 si = *(const f32x4 *)&sN[WT * wr + 32 * a + 8 * q + 4 * (l >> 5)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float s = si[u] + sj;
-                const float v = __builtin_fmaf(-2.f * inv2, acc[a][4 * q + u], s);
-                acc[a][4 * q + u] = v;
-                near |= !(v >= __builtin_fmaf(s, kGramNear, 0x1p-90f));
-            }
-        }
-    uint32_t m = 0;                        // this lane's near pairs: bit 16 a + r
-    if (!direct && work && __any(near)) {
-        int o = 0;                         // keeps the sums above from being held
-        asm volatile("" : "+v"(o));
-#pragma unroll
-        for (int a = 0; a < WA; ++a)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int dr = 32 * a + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-                const float s = sN[o + WT * wr + dr] + sj;
-                if (!(acc[a][r] >= __builtin_fmaf(s, kGramNear, 0x1p-90f)) && j < R0 + dr &&
-                    R0 + dr < n)
-                    m |= 1u << (16 * a + r);
-            }
-        if (__any(__popc(m) > kGramLaneNear) && l == 0) sMany = NT;
-    }
-    __syncthreads();
-    if (sMany > NT / 4) {
-        // groups of 256 threads take the tile's 64 x 64 quarters
-        const int g = w >> 2;
-        float *const q = (float *)lds + g * EdmF32Shape<64>::LDS_FLOATS;
-        if (WA == 1) {
-            edm_f32_tile_body<64, kEdmStageScalar>(p.t, bi, bj, q, t & 255);
-        } else {
-            for (int c = 0; c < 2; ++c)
-                edm_f32_tile_body<64, kEdmStageScalar>(p.t, 2 * bi + g, 2 * bj + c, q, t & 255);
-        }
-        return;
-    }
-    if (!work) return;
-    char *const ob = (char *)(p.t.out + (uint64_t)R0 * (uint64_t)(R0 - 1) / 2);
-    if (C0 + 31 < R0 && R0 + WT - 1 < n)
-        gram_store<true, WA>(ob, acc, R0, j, n, l);
-    else
-        gram_store<false, WA>(ob, acc, R0, j, n, l);
-    while (m) {                            // over the values just stored, by the same lane
-        const int r = __builtin_ctz(m);
-        m &= m - 1;
-        const int32_t i = R0 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-        *(float *)(ob + (((uint32_t)((i - R0) * (i + R0 - 1)) / 2u + (uint32_t)j) << 2)) =
-            __builtin_sqrtf(direct_d2_wide(p.t.x, ldx, d, i, j));
-    }
+    edm_gram_body<TILE>(p.t, bi, bj, sh, centre, (int)threadIdx.x);
 }
+
+static uint32_t gram_centre_bytes(int32_t d) { return (uint32_t)(d + kGramK - 1) / kGramK * kGramK * 4; }
 
 template <int MAP>
 static void edm_gram_tile(const tri_plan *p, const EdmArgs &a, hipStream_t s)
 {
     const dim3 grid(p->gx, p->gy);
-    const uint32_t centre = (uint32_t)(a.t.d + kGramK - 1) / kGramK * kGramK * 4;
+    const uint32_t centre = gram_centre_bytes(a.t.d);
     if (p->tile == 64) k_edm_gram<MAP, 64><<<grid, 256, centre, s>>>(a);
     else k_edm_gram<MAP, 128><<<grid, 512, centre, s>>>(a);
 }
@@ -2043,14 +1667,20 @@ static void edm_frag_launch(int S, const float *x, int32_t n, int32_t d, int64_t
 }
 
 // One distance-map domain under lambda with the FP32 body (batched
-// per-instance mode); false for an unsupported tile.
-bool launch_edm_f32_lambda(int tile, const TileGrid &g, const EdmTile &t, hipStream_t s)
+// per-instance mode; gram: with the products); false for an unsupported tile.
+bool launch_edm_f32_lambda(int tile, const TileGrid &g, const EdmTile &t, bool gram,
+                           hipStream_t s)
 {
     EdmArgs a{g, t};
     uint32_t gx, gy;
     if (g.T <= (1ull << 24)) { gx = (uint32_t)g.T; gy = 1; }
     else { gx = 1u << 16; gy = (uint32_t)((g.T + gx - 1) / gx); }
     const dim3 grid(gx, gy);
+    if (gram) {
+        if (tile != 64) return false;
+        k_edm_gram<MAP_LAMBDA, 64><<<grid, 256, gram_centre_bytes(t.d), s>>>(a);
+        return true;
+    }
     switch (tile) {
     case 16: k_edm_f32<MAP_LAMBDA, 16, kEdmStageScalar><<<grid, 256, 0, s>>>(a); return true;
     case 32: k_edm_f32<MAP_LAMBDA, 32, kEdmStageScalar><<<grid, 256, 0, s>>>(a); return true;
@@ -2109,9 +1739,8 @@ static tri_status edm_run(const tri_plan *p, const float *x, int64_t d, int64_t 
     hipStream_t s = (hipStream_t)stream;
     if (mode == TRI_EDM_FP32) {
         EdmArgs a{plan_tile_grid(p), EdmTile{(int32_t)p->n, (int32_t)d, ldx, x, out}};
-        // from kGramMinDims on the matrix cores are both nearer and faster (see
-        // k_edm_gram); its offsets within a tile are 32 bits, 128 rows of ldx
-        const bool gram = p->tile >= 64 && d >= kGramMinDims && ldx <= (1 << 22);
+        // where the matrix cores are both nearer and faster (see edm_gram_body)
+        const bool gram = edm_gram_takes(p->tile, d, ldx);
         a.g = plan_tile_grid_swizzled(p);
         if (!(gram ? edm_gram(p, a, s) : edm_f32(p, a, s))) return fail(TRI_E_UNSUPPORTED, "tri_edm: tile");
         TRI_HIP(hipGetLastError());

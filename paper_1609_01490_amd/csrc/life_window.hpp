@@ -117,15 +117,15 @@ __device__ __forceinline__ uint32_t life_upto(int32_t gi, int32_t jb)
 // domain (or the grid): loads are clamped, cells outside the domain are
 // cleared after staging and after every generation, and stores are tested.
 // Called by every wave of the workgroup, each with the EDGE its own rows need
-// (the barriers are the same number in both).  lds: S::WORDS words.
+// (the barriers are the same number in both).  wv, lane: the wave's number and
+// the lane's.  lds: S::WORDS words.
 template <int LX, int RR, int NW, bool EDGE>
 __device__ __forceinline__ void life_window_run(const LifeTile &p, int32_t i0, int32_t j0,
                                                 int32_t h, int32_t w, int32_t px, int gens,
-                                                int wv, uint32_t *lds)
+                                                int wv, int lane, uint32_t *lds)
 {
     using S = LifeWindow<LX, RR, NW>;
     const int32_t n = p.n, ld = (int32_t)p.ld;
-    const int lane = threadIdx.x & 63;
     const int x = lane & (LX - 1), y = lane / LX, q4 = lane & 3;
     // the first cell and row of the wave's part of the window
     const int32_t jw = j0 - px, iw = i0 - gens + wv * S::HW;
@@ -323,15 +323,15 @@ __device__ __forceinline__ void life_window_run(const LifeTile &p, int32_t i0, i
 template <int LX, int RR, int NW>
 __device__ __forceinline__ void life_window_body(const LifeTile &p, int32_t i0, int32_t j0,
                                                  int32_t h, int32_t w, int32_t px, int gens,
-                                                 int wv, uint32_t *lds)
+                                                 int wv, int lane, uint32_t *lds)
 {
     using S = LifeWindow<LX, RR, NW>;
     const int32_t jw = j0 - px, iw = i0 - gens + wv * S::HW;
     // every cell of the wave's rows is in the domain
     if (jw >= 0 && jw + S::W - 1 <= iw && iw + S::HW <= p.n)
-        life_window_run<LX, RR, NW, false>(p, i0, j0, h, w, px, gens, wv, lds);
+        life_window_run<LX, RR, NW, false>(p, i0, j0, h, w, px, gens, wv, lane, lds);
     else
-        life_window_run<LX, RR, NW, true>(p, i0, j0, h, w, px, gens, wv, lds);
+        life_window_run<LX, RR, NW, true>(p, i0, j0, h, w, px, gens, wv, lane, lds);
 }
 
 // Generations of one launch at most (on small grids the stencil takes more).

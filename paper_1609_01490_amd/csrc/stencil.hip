@@ -189,7 +189,8 @@ __global__ void __launch_bounds__(64 * NW) k_life_window(LifeTile t, int gens, i
     bi = __builtin_amdgcn_readfirstlane(bi);
     bj = __builtin_amdgcn_readfirstlane(bj);
     life_window_body<LX, RR, NW>(t, bi * h, bj * h, h, G * h, px, gens,
-                                 __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lds);
+                                 __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)),
+                                 (int)threadIdx.x & 63, lds);
 }
 
 template <int LX, int RR, int NW>

@@ -97,6 +97,25 @@ def test_batch_matches_oracle_and_modes(edm_tile, life_tile, flags, all16):
             assert (x.view(np.uint8) == y.view(np.uint8)).all()
 
 
+@pytest.mark.parametrize("life_tile,flags,all16", [(32, 0, False), (64, 32, True)])
+@pytest.mark.parametrize("d", [31, 33, 100, 512, 513])
+def test_batch_distance_dimensions(life_tile, flags, all16, d):
+    """Distance tiles of 64 on both sides of the dimensions that take products
+    (32 to 512), ragged ones among them: the FP32 bound, and the per-instance
+    launches' bits.  19 generations: one node of windows."""
+    tm = _tm()
+    spec = [("edm", 65), ("life", 300), ("edm", 66), ("edm", 2), ("edm", 200), ("life", 70)]
+    res = []
+    for how in (tm.BATCH_GRAPH, tm.BATCH_PER_INSTANCE):
+        note("batch dimensions", life_tile, flags, d, how)
+        b, host_in, A, B = _make(tm, spec, d, 19, 64, life_tile, seed=95, flags=flags, all16=all16)
+        b.launch(how)
+        res.append(_results(spec, A, B, 19))
+        _check_oracle(spec, host_in, res[-1], d, 19)
+    for x, y in zip(*res):
+        assert (x.view(np.uint8) == y.view(np.uint8)).all()
+
+
 def test_batch_graph_replays():
     """The graph is replayed several times with eager work in between; every
     replay must give the same (oracle-checked) result."""
