@@ -67,12 +67,18 @@ __device__ __forceinline__ void lds_barrier()
 // Error.  Rounding leaves about 2^-24 (|y_i|^2 + |y_j|^2) in d^2, whatever d,
 // while the direct sum's error grows with d.  A pair with d^2 < kGramNear of
 // that sum, or with a sum that is no finite number well inside FP32's range, is
-// recomputed from the differences in the direct body's order, and a tile with
-// many of them is left to the direct body, most of the time after 32 dimensions
-// (ten tight clusters in random order, where every tile is: d = 128 770 -> 1020
-// us, without the early test 1130; a hundred clusters 760 -> 510).  Against 64
-// bits, uniform points with 1 % near-duplicates, relative L2 and largest
-// relative error, direct / here:
+// recomputed from the differences in the direct body's order.  So is a pair whose
+// sum is small in scaled units: a coordinate below 1/4 keeps 2^-25 in its halves
+// and no relative precision, which adds up to 2^-24 sqrt(2 d S) to d^2, S the sum
+// of the scaled norms.  Points that were no samples can be that much closer
+// together than the samples (a few wide outliers among these, or samples that are
+// all zeros: errors of 1e-4 and more without this).  From S = kGramFloor d /
+// 1.625 on it is at most 0.64 of 2^-24 S; points spread as the samples have S of
+// about 10^4 d.  A tile with many pairs to recompute is left to the direct body,
+// most of the time after 32 dimensions (ten tight clusters in random order, where
+// every tile is: d = 128 770 -> 1020 us, without the early test 1130; a hundred
+// clusters 760 -> 510).  Against 64 bits, uniform points with 1 % near-duplicates,
+// relative L2 and largest relative error, direct / here:
 // 4.6e-8 / 3.9e-8 and 2.4e-7 / 2.6e-7 at d = 24, 5.2e-8 / 3.9e-8 and 2.9e-7 /
 // 2.4e-7 at d = 32, 6.4e-8 / 3.4e-8 and 3.7e-7 / 2.2e-7 at d = 63, 9.2e-8 /
 // 4.0e-8 and 4.8e-7 / 2.6e-7 at d = 128, 1.3e-7 / 3.5e-8 and 6.4e-7 / 2.5e-7 at
@@ -103,6 +109,7 @@ __device__ __forceinline__ void lds_barrier()
 // ---------------------------------------------------------------------------
 constexpr int kGramMinDims = 32;
 constexpr float kGramNear = 0.375f;
+constexpr float kGramFloor = 8.f;  // per dimension, on d^2 in scaled units
 constexpr int kGramK = 16;         // dimensions per staged chunk
 constexpr int kGramLaneNear = 4;   // near pairs per lane (of 32 or 16) that a tile may hold
 
@@ -336,6 +343,7 @@ __device__ __forceinline__ void edm_gram_body(const EdmTile &p, int32_t bi, int3
     // 2^30 are finite) makes its pairs' sums NaN, and those pairs near
     const float mi = norm(ni), mj = norm(nj);
     const float inv2 = 1.f / (sc * sc);
+    const float least = fmaxf(0x1p-90f, kGramFloor * (float)d * inv2);
     if (kq == 0) {
         sN[pt] = mi < 0x1p30f && mi * inv2 < 0x1p93f ? mi * inv2 : __builtin_nanf("");
         sN[TILE + pt] = mj < 0x1p30f && mj * inv2 < 0x1p93f ? mj * inv2 : __builtin_nanf("");
@@ -355,7 +363,7 @@ __device__ __forceinline__ void edm_gram_body(const EdmTile &p, int32_t bi, int3
                 const float s = si[u] + sj;
                 const float v = __builtin_fmaf(-2.f * inv2, acc[a][4 * q + u], s);
                 acc[a][4 * q + u] = v;
-                near |= !(v >= __builtin_fmaf(s, kGramNear, 0x1p-90f));
+                near |= !(v >= __builtin_fmaf(s, kGramNear, least));
             }
         }
     uint32_t m = 0;                        // this lane's near pairs: bit 16 a + r
@@ -368,7 +376,7 @@ __device__ __forceinline__ void edm_gram_body(const EdmTile &p, int32_t bi, int3
             for (int r = 0; r < 16; ++r) {
                 const int dr = 32 * a + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
                 const float s = sN[o + WT * wr + dr] + sj;
-                if (!(acc[a][r] >= __builtin_fmaf(s, kGramNear, 0x1p-90f)) && j < R0 + dr &&
+                if (!(acc[a][r] >= __builtin_fmaf(s, kGramNear, least)) && j < R0 + dr &&
                     R0 + dr < n)
                     m |= 1u << (16 * a + r);
             }

@@ -118,6 +118,69 @@ def test_edm_fp32_matrix_cores(tile, data):
         _check_rows(X, host(out), list(range(n)), tol)
 
 
+def _narrow_points(n, d, tile, data, seed):
+    """Points that lie far closer together than the 16 points that a tile takes
+    its centre and scale from (rows 1 + tile b + tile/8 u, columns tile b +
+    tile/8 u)."""
+    rng = np.random.default_rng(seed)
+    k = np.arange(n)
+    rows = (k - 1) % tile % (tile // 8) == 0
+    cols = k % tile % (tile // 8) == 0
+    kind, size = data.split()
+    X = rng.standard_normal((n, d))
+    if kind == "outliers":  # one pair of them in each tile row, which cancels
+        X[(k - 1) % tile == tile // 8, 0] = float(size)
+        X[(k - 1) % tile == tile // 4, 0] = -float(size)
+    elif kind == "equal":
+        X *= float(size)
+        X[rows | cols] = 0.25 if float(size) > 1e-7 else 0.0
+    else:  # spikes: one feature +-1 at the sampled points
+        X *= float(size)
+        X[rows | cols, 0] = np.where(k[rows | cols] % 2, 1.0, -1.0)
+    return X.astype(np.float32)
+
+
+_NARROW = ["outliers 1e5", "outliers 1e6", "outliers 1e7", "outliers 1e8", "equal 1", "equal 1e-3",
+           "equal 1e-6", "equal 1e-9", "equal 1e-12", "spikes 1e-3", "spikes 1e-5", "spikes 1e-7"]
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("data", _NARROW)
+def test_edm_fp32_samples_wider_than_the_points(tile, data):
+    """The scale of a tile's products comes from 16 of its points; where the
+    others are far smaller their pairs need the direct form.  The tolerance is
+    test_edm_fp32_matrix_cores's: the floor under the scaled norms adds 0.64 U S
+    to the 8 U S of the split, of which the halves' rounding takes 4."""
+    import torch
+    tm = _tm()
+    for n, d in ((65, 64), (300, 32), (400, 100)):
+        X = _narrow_points(n, d, tile, data, 4900 + d)
+        note("edm fp32 narrow", tile, data, n, d)
+        out = torch.full((n * (n - 1) // 2,), -1.0, dtype=torch.float32, device="cuda")
+        tm.Plan(n, tile, "lambda", include_diag=False).edm(dev(X), out, mode=tm.EDM_FP32)
+        tol = max(_fp32_bound(d), 4 / 3 * (d / 4 + 20) * U + 2 * U)
+        _check_rows(X, host(out), list(range(n)), tol)
+
+
+@pytest.mark.parametrize("data", _NARROW)
+def test_batch_distances_samples_wider_than_the_points(data):
+    """The same for the batch's distance tiles of 64."""
+    import torch
+    tm = _tm()
+    for d in (32, 100):
+        ns = [65, 300]
+        X = [_narrow_points(n, d, 64, data, 4950 + d) for n in ns]
+        out = [torch.full((n * (n - 1) // 2,), -1.0, dtype=torch.float32, device="cuda") for n in ns]
+        note("batch fp32 narrow", data, d)
+        b = tm.Batch([tm.KIND_EDM] * 2, ns, [d] * 2, edm_tile=64, life_tile=64, life_steps=0)
+        x = [dev(v) for v in X]
+        b.bind(x, out)
+        b.launch(tm.BATCH_GRAPH)
+        tol = max(_fp32_bound(d), 4 / 3 * (d / 4 + 20) * U + 2 * U)
+        for n, v, o in zip(ns, X, out):
+            _check_rows(v, host(o), list(range(n)), tol)
+
+
 @pytest.mark.parametrize("tile", [64, 128])
 @pytest.mark.parametrize("where", ["one point", "sampled point"])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
