@@ -128,23 +128,6 @@ __global__ void __launch_bounds__((CollideShape<TILE>::NT)) k_collide(CollideArg
 constexpr int kCollideWaves = 4;
 constexpr int kCollideThreads = 64 * kCollideWaves;
 
-// The run that starts at strip index k, tile (bi, bj): the number of its tiles.
-template <int MAP>
-__device__ __forceinline__ int collide_run(const TileGrid &g, const StripGrid &sg, uint32_t first,
-                                           int k, int32_t bi, int32_t bj)
-{
-    if constexpr (MAP == MAP_LAMBDA) {  // row-aligned: up to the diagonal
-        return min(sg.G - k, bi - bj + 1);
-    } else {
-        int len = 1;
-        for (; k + len < sg.G; ++len) {
-            int32_t ni, nj;
-            if (!strip_tile<MAP>(g, sg, first, k + len, ni, nj) || ni != bi || nj != bj + len) break;
-        }
-        return len;
-    }
-}
-
 template <int CTRL, int ROWS>
 __device__ __forceinline__ float dpp_of(float v)
 {
@@ -262,11 +245,12 @@ __global__ void __launch_bounds__(kCollideThreads, 4) k_collide_gram(CollideArgs
 
     for (int k = 0; k < sg.G;) {
         int32_t bi, bj;
+        if (MAP == MAP_BB && first + (uint32_t)k > blockIdx.y) return;  // above the diagonal
         k = strip_next<MAP>(p.g, sg, first, k, bi, bj);
         if (k >= sg.G) return;  // uniform over the workgroup
         bi = __builtin_amdgcn_readfirstlane(bi);
         bj = __builtin_amdgcn_readfirstlane(bj);
-        const int len = __builtin_amdgcn_readfirstlane(collide_run<MAP>(p.g, sg, first, k, bi, bj));
+        const int len = strip_run<MAP>(p.g.m, sg, (int32_t)first + k, (int32_t)blockIdx.y, k, bi, bj);
         k += len;
         const int32_t i0 = 1 + bi * TILE;
         if (bi != staged) {
@@ -409,11 +393,12 @@ __global__ void __launch_bounds__(kCollideThreads) k_collide_near(CollideArgs p,
 
     for (int k = 0; k < sg.G;) {
         int32_t bi, bj;
+        if (MAP == MAP_BB && first + (uint32_t)k > blockIdx.y) return;  // above the diagonal
         k = strip_next<MAP>(p.g, sg, first, k, bi, bj);
         if (k >= sg.G) return;  // uniform over the workgroup
         bi = __builtin_amdgcn_readfirstlane(bi);
         bj = __builtin_amdgcn_readfirstlane(bj);
-        const int len = __builtin_amdgcn_readfirstlane(collide_run<MAP>(p.g, sg, first, k, bi, bj));
+        const int len = strip_run<MAP>(p.g.m, sg, (int32_t)first + k, (int32_t)blockIdx.y, k, bi, bj);
         k += len;
         const int32_t i0 = 1 + bi * TILE;
         if (bi != staged) {
@@ -533,11 +518,13 @@ static void collide_filtered(const tri_plan *p, const CollideArgs &a0, hipStream
 // 6.0 / 8.0, 8000 13.7 / 13.6, 12000 22.9 / 17.4; tile 32 n = 3000 6.8 / 8.6,
 // 8000 20.0 / 15.1; tile 128 n = 1000 10.0 / 7.7, 20000 59.6 / 24.1; 1-D tile
 // 64 n = 9000 11.8 / 14.8, 12000 16.9 / 17.0, 20000 35.8 / 26.7; tile 128
-// n = 8000 11.3 / 12.4, 20000 34.3 / 26.8; tile 32 n = 8000 17.9 / 15.0.
+// n = 8000 11.3 / 12.4, 20000 34.3 / 26.8; tile 32 n = 7000 14.0 / 15.3 (3-D 14.8 /
+// 15.4), 8000 17.9 / 15.0.  The other maps cross at the same sizes or below (tile
+// 32, 1-D: RB n = 6200 11.7 / 13.9, 7000 12.9 / 12.9, BB 7000 16.2 / 10.3).
 static bool collide_filters(const tri_plan *p, int dim)
 {
     switch (p->tile) {
-    case 32: return p->n >= 6144;
+    case 32: return p->n >= 7424;
     case 64: return p->n >= (dim == 3 ? 9216 : 13312);
     case 128: return dim == 3 || p->n >= 13312;
     }

@@ -103,6 +103,27 @@ def test_collide_filters_miss_nothing(tile, kind):
                 assert (host(counts) == exp).all(), (kind, tile, map_name, n, dim)
 
 
+@pytest.mark.parametrize("map_name,even", [("lambda", True), ("bb", False), ("rb", True),
+                                           ("rb", False), ("rec", True)])
+@pytest.mark.parametrize("tile", [32, 64, 128])
+def test_collide_runs_of_every_map(tile, map_name, even):
+    """The filtered kernels' runs of neighbouring tiles under each map: m even
+    and odd (RB folds differently; its folded part runs from right to left
+    when m is odd), REC's levels, the last strip of a row short."""
+    import torch
+    tm = _tm()
+    m = {32: 234, 64: 210, 128: 106}[tile] + (0 if even else 1)
+    if map_name == "rec":
+        m = 16384 // tile
+    n = m * tile - tile // 2
+    for dim in (1, 3):
+        S = inputs.spheres(n, dim, mean_degree=6.0, seed=5400 + n + dim)
+        note("collide runs", map_name, tile, n, dim)
+        counts = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        tm.Plan(n, tile, map_name, include_diag=False).collide(dev(S), counts, dim=dim)
+        assert (host(counts) == oracle.collide(S, dim)).all(), (map_name, tile, n, dim)
+
+
 def test_collide_errors():
     import torch
     tm = _tm()
