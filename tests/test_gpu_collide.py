@@ -124,6 +124,28 @@ def test_collide_runs_of_every_map(tile, map_name, even):
         assert (host(counts) == oracle.collide(S, dim)).all(), (map_name, tile, n, dim)
 
 
+@pytest.mark.parametrize("map_name", ["lambda", "bb", "rb", "rec"])
+@pytest.mark.parametrize("tile", [32, 64, 128])
+def test_collide_most_pairs_overlap(tile, map_name):
+    """Half of all pairs and nearly all: the filters' counts of rows (kept over
+    a strip's runs of one tile row) and of columns."""
+    import torch
+    tm = _tm()
+    for n in ((8192 if tile == 32 else 16384 if tile == 64 else 1024), 8191 if tile < 64 else 9999):
+        m = -(-(n - 1) // tile)
+        if map_name == "rec" and m & (m - 1):
+            continue
+        for radius in (0.35, 1.0):
+            rng = np.random.default_rng(n + tile)
+            S = np.zeros((n, 4), dtype=np.float32)
+            S[:, :3] = rng.random((n, 3), dtype=np.float32)
+            S[:, 3] = np.float32(radius) * rng.random(n, dtype=np.float32)
+            note("collide dense", map_name, tile, n, radius)
+            counts = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+            tm.Plan(n, tile, map_name, include_diag=False).collide(dev(S), counts, dim=3)
+            assert (host(counts) == oracle.collide(S, 3)).all(), (map_name, tile, n, radius)
+
+
 def test_collide_errors():
     import torch
     tm = _tm()
