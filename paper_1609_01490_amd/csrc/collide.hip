@@ -233,7 +233,7 @@ __global__ void __launch_bounds__(kCollideThreads, 4) k_collide_gram(CollideArgs
     __shared__ f4 rows[TILE];
     __shared__ u32x4 terms[TILE];
     __shared__ float red[2][8];
-    __shared__ int32_t hits[TILE];  // overlaps of the staged rows
+    __shared__ int32_t hits[kCollideWaves][TILE];  // a wave's overlaps per row of a block
 
     const int t = threadIdx.x, l = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -244,32 +244,22 @@ __global__ void __launch_bounds__(kCollideThreads, 4) k_collide_gram(CollideArgs
     CollideBox box{};
     h4 A[NB];
 
-    for (int k = 0;;) {
-        int32_t bi = 0, bj = 0;
-        if (MAP == MAP_BB && first + (uint32_t)k > blockIdx.y) k = sg.G;  // above the diagonal
+    for (int k = 0; k < sg.G;) {
+        int32_t bi, bj;
+        if (MAP == MAP_BB && first + (uint32_t)k > blockIdx.y) return;  // above the diagonal
         k = strip_next<MAP>(p.g, sg, first, k, bi, bj);
-        const bool more = k < sg.G;  // (uniform over the workgroup)
+        if (k >= sg.G) return;  // uniform over the workgroup
         bi = __builtin_amdgcn_readfirstlane(bi);
         bj = __builtin_amdgcn_readfirstlane(bj);
-        if (staged >= 0 && (!more || bi != staged)) {
-            // the runs of these rows are done (the wait for the last LDS additions
-            // said explicitly: the compiler leaves it out before this barrier)
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-            __syncthreads();
-            if (t < TILE && hits[t]) atomicAdd(&p.counts[1 + staged * TILE + t], hits[t]);
-        }
-        if (!more) return;
         const int len = strip_run<MAP>(p.g.m, sg, (int32_t)first + k, (int32_t)blockIdx.y, k, bi, bj);
         k += len;
         const int32_t i0 = 1 + bi * TILE;
         if (bi != staged) {
+            if (staged >= 0) __syncthreads();  // the previous run is done with the LDS
             staged = bi;
             f4 v{nan, nan, nan, nan};
             if (t < TILE && i0 + t < n) v = p.s[i0 + t];
-            if (t < TILE) {
-                rows[t] = v;
-                hits[t] = 0;
-            }
+            if (t < TILE) rows[t] = v;
             if (w < (TILE + 63) / 64) {
                 const float far = 0x1p60f, none = -3.0e38f;
                 const bool ux = __builtin_fabsf(v.x) < far, uy = __builtin_fabsf(v.y) < far,
@@ -348,11 +338,7 @@ __global__ void __launch_bounds__(kCollideThreads, 4) k_collide_gram(CollideArgs
                     any |= neg[a];
                 }
                 if (!__any((int32_t)any < 0)) continue;
-                // rare: the exact test of the pairs that passed, each lane its
-                // own.  The rows' overlaps are counted in LDS and added to the
-                // counts once per run, a column's once per block: with most
-                // pairs overlapping, two global additions for each took n =
-                // 1000, tile 128 733 us (the exact test of every pair 280)
+                // rare: the exact test of the pairs that passed, each lane its own
                 const int32_t j = cb + 32 * b + (l & 31);
                 const bool live = j < c1;
                 const f4 cj = p.s[live ? j : cb];
@@ -369,17 +355,40 @@ __global__ void __launch_bounds__(kCollideThreads, 4) k_collide_gram(CollideArgs
                     m |= (uint64_t)ma << (16 * a);
                 }
                 if (!live) m = 0;
-                int32_t mine = 0;
+                // Where most lanes have some, the rows' overlaps are counted in the
+                // wave's own LDS and added to the counts once per block.  (Two
+                // additions to memory for each overlap, nearly all pairs
+                // overlapping: n = 1000, tile 128 733 us, in this form 43; the
+                // exact test of every pair takes 280.)
+                if (__builtin_popcountll(__ballot(m != 0)) > 16) {
+                    for (int q = l; q < TILE; q += 64) hits[w][q] = 0;
+                    __builtin_amdgcn_wave_barrier();
+                    int32_t mine = 0;
+                    while (m) {
+                        const int k = __builtin_ctzll(m), r = k & 15;
+                        m &= m - 1;
+                        const int row = 32 * (k >> 4) + 8 * (r >> 2) + (r & 3) + r0;
+                        if (j < i0 + row && overlap<3>(rows[row], cj)) {
+                            atomicAdd(&hits[w][row], 1);
+                            ++mine;
+                        }
+                    }
+                    if (mine) atomicAdd(&p.counts[j], mine);
+                    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's additions
+                    __builtin_amdgcn_wave_barrier();
+                    for (int q = l; q < TILE; q += 64)
+                        if (const int32_t c = hits[w][q]) atomicAdd(&p.counts[i0 + q], c);
+                    continue;
+                }
                 while (m) {
                     const int k = __builtin_ctzll(m), r = k & 15;
                     m &= m - 1;
                     const int row = 32 * (k >> 4) + 8 * (r >> 2) + (r & 3) + r0;
                     if (j < i0 + row && overlap<3>(rows[row], cj)) {
-                        atomicAdd(&hits[row], 1);
-                        ++mine;
+                        atomicAdd(&p.counts[i0 + row], 1);
+                        atomicAdd(&p.counts[j], 1);
                     }
                 }
-                if (mine) atomicAdd(&p.counts[j], mine);
             }
         }
     }
