@@ -520,7 +520,7 @@ static int32_t collide_strip_len(const tri_plan *p)
 {
     int32_t G = 64;
     while (G > kCollideThreads / p->tile && p->T / G < 1536) G /= 2;
-    return G;
+    return p->map == TRI_MAP_LAMBDA ? strip_len_that_fits((int32_t)p->m, G, kCollideThreads) : G;
 }
 
 template <int MAP, int TILE, int DIM>

@@ -781,7 +781,10 @@ static void launch_tile(const tri_plan *p, const ElemArgs &args, hipStream_t s)
     const dim3 grid(p->gx, p->gy);
     if constexpr (ROWS == kLines && OP != TRI_OP_AXPYT_F32) {
         static_assert(TILE >= 32, "whole lines");
-        k_lines<OP, MAP, TILE><<<grid, 8 * TILE, 0, s>>>(args);
+        ElemArgs a = args;
+        dim3 lines = grid;
+        if constexpr (MAP == MAP_LAMBDA) grid_that_fits(a.g, 8 * TILE, lines);
+        k_lines<OP, MAP, TILE><<<lines, 8 * TILE, 0, s>>>(a);
     } else {
         constexpr bool VECTOR = ROWS != kScalar;
         constexpr bool STREAM = ROWS == kStream || ROWS == kStreamLong;

@@ -387,6 +387,34 @@ __host__ __forceinline__ StripGrid strip_grid(int map, int32_t m, uint32_t flags
     return s;
 }
 
+// Whether one grid dimension takes so many blocks of so many threads: fewer
+// than 2^32 work-items.
+inline bool grid_x_fits(uint64_t blocks, uint32_t threads)
+{
+    return blocks * threads < (1ull << 32);
+}
+
+// The strip length, from G upwards by doubling, at which the row-aligned strips of
+// m tile rows fit one grid dimension.
+inline int32_t strip_len_that_fits(int32_t m, int32_t G, uint32_t threads)
+{
+    while (!grid_x_fits(strip_align_prefix((uint32_t)m, (uint32_t)G), threads)) G *= 2;
+    return G;
+}
+
+// The grid of a kernel with more threads a block than the plan's 1-D lambda grid
+// allows for: rows of 2^16 blocks, as plans of more tiles have.
+inline void grid_that_fits(TileGrid &g, uint32_t threads, dim3 &grid)
+{
+    if (grid_x_fits(grid.x, threads)) return;
+    g.flags &= ~kLambda24;
+    if (!(g.flags & (TRI_FLAG_XCD_SWIZZLE | TRI_FLAG_ORDER_REVERSE | TRI_FLAG_ORDER_PAIRS |
+                     TRI_FLAG_SQRT_RSQ | TRI_FLAG_SQRT_F64 | TRI_FLAG_SQRT_NEWTON |
+                     TRI_FLAG_SQRT_EPS)))
+        g.flags |= kLambda32;
+    grid = dim3(1u << 16, (uint32_t)((g.T + 0xFFFFu) >> 16));
+}
+
 // First tile number of this workgroup's strip; its tile t is first + t K.
 template <int MAP>
 __device__ __forceinline__ uint32_t strip_first(const TileGrid &g, const StripGrid &sg)

@@ -54,8 +54,38 @@ static void check_runs(int32_t m, int32_t gx, int32_t gy, int32_t G)
             CHECK(seen[(size_t)i * m + j] == (j <= i), "map %d m %d G %d tile %d %d", MAP, m, G, i, j);
 }
 
+// Launches of more than 2^32 work-items along x are refused by the hardware's grid.
+static void check_limits()
+{
+    for (uint32_t threads : {256u, 512u, 1024u})
+        for (int32_t m : {1, 100, 4096, 5792, 5793, 8192, 46875, 92681})
+            for (int32_t G : {2, 8, 64}) {
+                const int32_t L = strip_len_that_fits(m, G, threads);
+                CHECK(L >= G && strip_align_prefix((uint32_t)m, (uint32_t)L) * threads < (1ull << 32),
+                      "m %d G %d threads %u: %d", m, G, threads, L);
+                CHECK(L == G || strip_align_prefix((uint32_t)m, (uint32_t)L / 2) * threads >= (1ull << 32),
+                      "m %d G %d threads %u: %d is longer than needed", m, G, threads, L);
+            }
+    for (uint32_t flags : {0u, (uint32_t)TRI_FLAG_XCD_SWIZZLE, (uint32_t)TRI_FLAG_ORDER_PAIRS})
+        for (uint32_t threads : {256u, 512u, 1024u})
+            for (uint32_t T : {1u, 1000u, (1u << 22) - 1, 1u << 22, (1u << 23) + 1, 1u << 24}) {
+                TileGrid g{1, flags | (flags <= 1u ? kLambda24 : 0u), T};
+                dim3 grid(T);
+                grid_that_fits(g, threads, grid);
+                CHECK((uint64_t)grid.x * threads < (1ull << 32) && grid.y < 65536u, "T %u", T);
+                CHECK((uint64_t)grid.x * grid.y >= T, "T %u", T);
+                if (grid.y > 1) {
+                    CHECK(grid.x == (1u << 16) && !(g.flags & kLambda24), "T %u", T);
+                    CHECK(((g.flags & kLambda32) != 0) == (flags == 0), "T %u flags %u", T, flags);
+                } else if (grid.x != (1u << 16)) {
+                    CHECK(grid.x == T, "T %u", T);
+                }
+            }
+}
+
 int main()
 {
+    check_limits();
     for (int32_t G : {2, 4, 8, 64})
         for (int32_t m = 1; m <= 130; ++m) {
             check_runs<MAP_BB>(m, m, m, G);

@@ -146,6 +146,27 @@ def test_collide_most_pairs_overlap(tile, map_name):
             assert (host(counts) == oracle.collide(S, 3)).all(), (map_name, tile, n, radius)
 
 
+@pytest.mark.slow
+@pytest.mark.parametrize("dim", [1, 3])
+@pytest.mark.parametrize("n,tile", [(1_500_000, 32), (2_960_000, 32)])
+def test_collide_beyond_the_usual_grids(n, tile, dim):
+    """More strips than one grid dimension takes at the usual length, up to the
+    most tiles that a plan has (just below 2^32): the counts of a launch with
+    tiles of 128."""
+    import torch
+    tm = _tm()
+    S = dev(inputs.spheres(n, dim, seed=5500 + dim))
+    got = []
+    for t in (tile, 128):
+        note("collide large", n, t, dim)
+        counts = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        tm.Plan(n, t, "lambda", include_diag=False).collide(S, counts, dim=dim)
+        torch.cuda.synchronize()
+        got.append(counts)
+    assert torch.equal(*got)
+    assert 2.0 < got[1].double().mean().item() < 6.0
+
+
 def test_collide_errors():
     import torch
     tm = _tm()
