@@ -182,6 +182,36 @@ def test_batch_distances_samples_wider_than_the_points(data):
 
 
 @pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("top,d,unit,offset", [
+    (255, 32, 1, 0), (255, 50, 1, 0), (255, 128, 2.0 ** -8, 0), (255, 250, 1, 0),
+    (140, 784, 1, 0), (1, 64, 1, 0), (1, 1000, 1, 0), (3, 100, 2.0 ** 40, 0), (17, 300, 0.125, 0),
+    (700, 40, 1, 0), (255, 96, 1, 2.0 ** 16)])
+def test_edm_fp32_whole_numbers_are_exact(tile, top, d, unit, offset):
+    """Coordinates k * unit, k = 0 .. top: the squares sum to whole numbers of
+    units^2.  With the centre within top / 2 + top / 32 of every coordinate the
+    two norms sum to less than 2 d (0.54 top)^2 < 2^24, so that nothing is
+    rounded but the root."""
+    import torch
+    tm = _tm()
+    assert 2 * d * (0.54 * top) ** 2 < 2 ** 24
+    n = 300
+    rng = np.random.default_rng(5000 + d)
+    k = rng.integers(0, top + 1, (n, d))
+    k[::29] = k[3]
+    X = (k * unit + offset).astype(np.float32)
+    assert (X.astype(np.float64) == k * unit + offset).all()
+    note("edm fp32 whole numbers", tile, top, d, unit, offset)
+    out = torch.full((n * (n - 1) // 2,), -1.0, dtype=torch.float32, device="cuda")
+    tm.Plan(n, tile, "lambda", include_diag=False).edm(dev(X), out, mode=tm.EDM_FP32)
+    i, j = np.tril_indices(n, -1)
+    sq = ((k[i] - k[j]) ** 2).sum(1)
+    # (the root of a whole number below 2^24 rounds to FP32 through FP64 as directly)
+    want = (np.sqrt(sq.astype(np.float64)) * unit).astype(np.float32)
+    got = host(out)
+    assert (got == want).all(), (int((got != want).sum()), got[got != want][:4], want[got != want][:4])
+
+
+@pytest.mark.parametrize("tile", [64, 128])
 @pytest.mark.parametrize("where", ["one point", "sampled point"])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_edm_fp32_matrix_cores_not_finite(tile, where, value):
