@@ -1029,9 +1029,9 @@ struct EdmTile {
     float *out;
 };
 
-template <int TILE>
+template <int TILE, int THREADS = 256>
 struct EdmF32Shape {
-    static constexpr int NT = 256;
+    static constexpr int NT = THREADS;
     static constexpr int TX = 16;                  // lanes along columns
     static constexpr int TY = NT / TX;             // lanes along rows
     static constexpr int RB = TILE / TY;           // register rows per lane (contiguous)
@@ -1083,14 +1083,14 @@ __device__ __forceinline__ void lds_read_rows(const float *src, float (&dst)[RB]
 // kEdmStageVec4: the same with 16-byte loads at 32-bit byte offsets from the
 // base (needs d and ldx multiples of 4, a 16-byte aligned x and
 // n * ldx * 4 < 2^31): a quarter of the loads and of their address
-// registers.  tid: the lane's number among the 256 that share the tile.
+// registers.  tid: the lane's number among the THREADS that share the tile.
 enum { kEdmStageLoop = 0, kEdmStageScalar = 1, kEdmStageVec4 = 2 };
 
-template <int TILE, int STAGE = kEdmStageScalar>
+template <int TILE, int STAGE = kEdmStageScalar, int THREADS = 256>
 __device__ __forceinline__ void edm_f32_tile_body(const EdmTile &p, int32_t bi, int32_t bj,
                                                   float *lds, int tid)
 {
-    using S = EdmF32Shape<TILE>;
+    using S = EdmF32Shape<TILE, THREADS>;
     float *XI = lds;                  // [K][LD]
     float *XJ = lds + S::K * S::LD;   // [K][LD]
     const int32_t n = p.n, d = p.d;

@@ -81,9 +81,12 @@ __device__ __forceinline__ void lds_barrier()
 // all zeros: errors of 1e-4 and more without this).  From S = kGramFloor d /
 // 1.625 on it is at most 0.64 of 2^-24 S; points spread as the samples have S of
 // about 10^4 d.  A tile with many pairs to recompute is left to the direct body,
-// most of the time after 32 dimensions (ten tight clusters in random order, where
-// every tile is: d = 128 770 -> 1020 us, without the early test 1130; a hundred
-// clusters 760 -> 510).  Against 64 bits, uniform points with 1 % near-duplicates,
+// most of the time after 32 dimensions.  Where every tile is (ten tight clusters in
+// random order), that costs what was tried before: n = 16384 against the direct
+// form alone, tile 128 d = 128 715 -> 835 us, d = 64 410 -> 485, tile 64 780 -> 912 and
+// 433 -> 543; from about sixty clusters on the products win again (tile 128, d = 128
+// 720 -> 618, a hundred 485).  In four quarters of 64 x 64 tile 128's direct body
+// took 970 us, without the early test 1130.  Against 64 bits, uniform points with 1 % near-duplicates,
 // relative L2 and largest relative error, direct / here:
 // 4.6e-8 / 3.9e-8 and 2.4e-7 / 2.6e-7 at d = 24, 5.2e-8 / 3.9e-8 and 2.9e-7 /
 // 2.4e-7 at d = 32, 6.4e-8 / 3.4e-8 and 3.7e-7 / 2.2e-7 at d = 63, 9.2e-8 /
@@ -123,7 +126,7 @@ template <int TILE>
 struct GramLds {
     static constexpr int kPlane = TILE * kGramK * 2;  // bytes
     static constexpr int kBuffer = kPlane * 4;
-    static constexpr int kDirect = (TILE / 64) * EdmF32Shape<64>::LDS_FLOATS * 4;
+    static constexpr int kDirect = EdmF32Shape<TILE, 4 * TILE>::LDS_FLOATS * 4;
     static constexpr int kBytes = kBuffer * 2 > kDirect ? kBuffer * 2 : kDirect;
     __attribute__((aligned(16))) unsigned char operands[kBytes];
     __attribute__((aligned(16))) float norms[2 * TILE];
@@ -394,15 +397,7 @@ __device__ __forceinline__ void edm_gram_body(const EdmTile &p, int32_t bi, int3
     }
     __syncthreads();
     if (sMany > NT / 4) {
-        // groups of 256 threads take the tile's 64 x 64 quarters
-        const int g = w >> 2;
-        float *const q = (float *)lds + g * EdmF32Shape<64>::LDS_FLOATS;
-        if (WA == 1) {
-            edm_f32_tile_body<64, kEdmStageScalar>(p, bi, bj, q, t & 255);
-        } else {
-            for (int c = 0; c < 2; ++c)
-                edm_f32_tile_body<64, kEdmStageScalar>(p, 2 * bi + g, 2 * bj + c, q, t & 255);
-        }
+        edm_f32_tile_body<TILE, kEdmStageScalar, NT>(p, bi, bj, (float *)lds, t);
         return;
     }
     if (!work) return;

@@ -212,6 +212,26 @@ def test_edm_fp32_whole_numbers_are_exact(tile, top, d, unit, offset):
 
 
 @pytest.mark.parametrize("tile", [64, 128])
+def test_edm_fp32_tiles_left_to_the_direct_body(tile):
+    """Two tight clusters: half of every tile's pairs are near, so that each tile
+    is left to the direct body of its own size; the bits are tile 32's, whose
+    sums run in the same order."""
+    import torch
+    tm = _tm()
+    rng = np.random.default_rng(5100)
+    for n, d, pad in ((130, 33, 0), (257, 64, 1), (300, 130, 2), (391, 50, 0)):
+        X = np.full((n, d + pad), np.nan, dtype=np.float32)
+        X[:, :d] = rng.random((2, d))[rng.integers(0, 2, n)] + 0.001 * rng.random((n, d))
+        got = []
+        for t in (tile, 32):
+            note("edm fp32 direct tiles", t, n, d, pad)
+            out = torch.full((n * (n - 1) // 2,), -1.0, dtype=torch.float32, device="cuda")
+            tm.Plan(n, t, "lambda", include_diag=False).edm(dev(X)[:, :d], out, mode=tm.EDM_FP32)
+            got.append(host(out).view(np.uint32))
+        assert (got[0] == got[1]).all(), (n, d, int((got[0] != got[1]).sum()))
+
+
+@pytest.mark.parametrize("tile", [64, 128])
 @pytest.mark.parametrize("where", ["one point", "sampled point"])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_edm_fp32_matrix_cores_not_finite(tile, where, value):
