@@ -130,7 +130,7 @@ enum {
 
 /* Distance-map arithmetic. */
 enum {
-    TRI_EDM_FP32 = 0,   /* FP32: the direct sum of squared differences, or nearer   */
+    TRI_EDM_FP32 = 0,   /* FP32: direct sum of squared differences, or split Gram   */
     TRI_EDM_BF16X3 = 1, /* centred split-BF16 Gram on MFMA (hi*hi + hi*lo + lo*hi)  */
     TRI_EDM_BF16 = 2    /* centred single-BF16 Gram on MFMA (faster, less accurate) */
 };
@@ -284,9 +284,18 @@ tri_status tri_launch_stencil(const tri_plan *plan, uint8_t *cur, uint8_t *nxt, 
  * n x d FP32 (1 <= d <= 4096), leading dimension ldx >= d, 4-byte aligned.
  * mode is a TRI_EDM_* value:
  *  - TRI_EDM_FP32: plan tile 16, 32, 64 or 128; no workspace (ws may be NULL).
- *    From 32 dimensions on, tiles of 64 and 128 take d^2 from FP32 norms about
- *    a centre of the tile and a split product on the matrix cores, whose error
- *    is below the direct sum's; near pairs and tiles out of range are direct.
+ *    The direct sum's distances are within (d / 2 + 2) 2^-24 of the exact
+ *    ones, relative to them.  From 32 dimensions on, tiles of 64 and 128 take
+ *    d^2 from FP32 norms about a centre of the tile and a split product on the
+ *    matrix cores, within (5 d / 12 + 24) 2^-24; near pairs, pairs far smaller
+ *    than their tile's spread and sums out of range are direct.  Measured on
+ *    uniform, normal, log-normal and unit vectors the largest error is about
+ *    the direct sum's at d = 32 and less from there on (uniform points d =
+ *    128: 2.6e-7, direct 4.8e-7), and the root mean square is less throughout;
+ *    on features that are mostly zeros the largest is up to twice the direct
+ *    sum's below d = 96.  Whole multiples of a power of two whose norms about
+ *    the centre sum to less than 2^24 of its squares give the correctly rounded
+ *    distances in both forms.
  *  - TRI_EDM_BF16X3 / TRI_EDM_BF16: plan tile 128; `out` 16-byte aligned
  *    (rows are written as 16-byte vectors); ws a device buffer of at least
  *    tri_edm_workspace_size() bytes, 256-byte aligned, else TRI_E_NOMEM /

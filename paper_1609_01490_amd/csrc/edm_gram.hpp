@@ -66,7 +66,7 @@ __device__ __forceinline__ void lds_barrier()
 // of 16 put pixels off their grid: d = 32 33000 of 530000 distances wrongly
 // rounded, d = 784 all but a few).
 // The norms are FP32 sums of the squares of y.  The products take y as two
-// FP16 values, h + l (22 significant bits or more; spreads up to 2^7 times the
+// FP16 values, h + l (23 significant bits or 2^-25; spreads up to 2^7 times the
 // samples' fit, see the norm test): h.l + l.h + h.h accumulated in FP32 by
 // v_mfma_f32_32x32x16_f16.
 //
@@ -80,20 +80,34 @@ __device__ __forceinline__ void lds_barrier()
 // together than the samples (a few wide outliers among these, or samples that are
 // all zeros: errors of 1e-4 and more without this).  From S = kGramFloor d /
 // 1.625 on it is at most 0.64 of 2^-24 S; points spread as the samples have S of
-// about 10^4 d.  A tile with many pairs to recompute is left to the direct body,
-// most of the time after 32 dimensions.  Where every tile is (ten tight clusters in
-// random order), that costs what was tried before: n = 16384 against the direct
-// form alone, tile 128 d = 128 715 -> 835 us, d = 64 410 -> 485, tile 64 780 -> 912 and
-// 433 -> 543; from about sixty clusters on the products win again (tile 128, d = 128
-// 720 -> 618, a hundred 485).  In four quarters of 64 x 64 tile 128's direct body
-// took 970 us, without the early test 1130.  Against 64 bits, uniform points with 1 % near-duplicates,
-// relative L2 and largest relative error, direct / here:
+// about 10^4 d.
+//
+// In units of 2^-24 S the rest is at most d / 8 + 4 for the norms' sums, 4 for the
+// coordinates' rounding, 4 for their halves' (2^-23 of a coordinate), 4 for the
+// product l.l that is left out, and 3 d / 16 for the products' sums (one rounding
+// per instruction): with S <= 8/3 d^2 a distance is within (5 d / 12 + 24) 2^-24 of
+// the exact one relative to it, near pairs within the direct sum's (d / 2 + 2)
+// 2^-24, which is the smaller bound up to d = 264.  These bounds are far off: what
+// is found, against 64 bits, uniform points with 1 % near-duplicates, relative
+// L2 and largest relative error, direct / here, is
 // 4.6e-8 / 3.9e-8 and 2.4e-7 / 2.6e-7 at d = 24, 5.2e-8 / 3.9e-8 and 2.9e-7 /
 // 2.4e-7 at d = 32, 6.4e-8 / 3.4e-8 and 3.7e-7 / 2.2e-7 at d = 63, 9.2e-8 /
 // 4.0e-8 and 4.8e-7 / 2.6e-7 at d = 128, 1.3e-7 / 3.5e-8 and 6.4e-7 / 2.5e-7 at
 // d = 256; d = 128 in clusters of 0.6 times their centres' spread 9.1e-8 /
 // 4.0e-8 and 4.5e-7 / 3.7e-7.  Hence the line at 32: below it the largest error
-// would be larger than the direct sum's.
+// would be larger than the direct sum's.  Normal, log-normal, Laplace and unit
+// vectors are like it.  Features that are mostly zeros are the exception, since few
+// terms of the direct sum round (a normal variable less 0.8, cut at zero, 8
+// million pairs, L2 and largest): d = 32 3.8e-8 / 3.8e-8 and 2.2e-7 / 3.9e-7, d =
+// 63 4.5e-8 / 3.7e-8 and 2.6e-7 / 3.5e-7, d = 96 5.3e-8 / 3.8e-8 and 3.2e-7 / 3.3e-7.
+//
+// A tile with many pairs to recompute is left to the direct body, most of the
+// time after 32 dimensions.  Where every tile is (ten tight clusters in random
+// order), that costs what was tried before: n = 16384 against the direct form
+// alone, tile 128 d = 128 715 -> 835 us, d = 64 410 -> 485, tile 64 780 -> 912 and 433 ->
+// 543; from about sixty clusters on the products win again (tile 128, d = 128 720 ->
+// 618, a hundred 485).  In four quarters of 64 x 64 tile 128's direct body took 970
+// us, without the early test 1130.
 //
 // Work.  The direct form is bound by two vector operations per pair and
 // dimension.  Here they are about 5 per staged coordinate and 10 per pair, and
@@ -140,7 +154,7 @@ __device__ __forceinline__ int gram_slot(int point, int q)
     return point * (kGramK * 2) + 16 * (q ^ ((point >> 3) & 1));
 }
 
-// v = h + l to 22 significant bits or 2^-25, whichever is coarser.
+// v = h + l to 23 significant bits or 2^-25, whichever is coarser.
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
