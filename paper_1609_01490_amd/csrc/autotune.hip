@@ -97,7 +97,21 @@ __global__ void __launch_bounds__(256) k_tune_fill(float *x, int64_t count)
     x[q] = (float)(h >> 8) * (1.0f / 16777216.0f);
 }
 
-static std::vector<Candidate> candidates(int workload, int64_t n)
+// Whether the workload's launches (rows of ld elements) take the plan's order of
+// omega at this tile; where they do not, candidates that differ in it alone would
+// be the same launch.
+static bool order_acts(int workload, int tile, int64_t ld)
+{
+    switch (workload) {
+    case TRI_TUNE_EDM_FP32: return false;
+    case TRI_TUNE_ELEMENTWISE_F32: return ld % 32 == 0;
+    case TRI_TUNE_ELEMENTWISE_I32: return ld % 32 == 0 || tile >= 32;
+    }
+    return true;
+}
+
+// ld: the pitch of the tuner's rows
+static std::vector<Candidate> candidates(int workload, int64_t ld)
 {
     std::vector<int> tiles;
     std::vector<int> maps = {TRI_MAP_BB, TRI_MAP_RB, TRI_MAP_REC, TRI_MAP_LAMBDA};
@@ -113,7 +127,7 @@ static std::vector<Candidate> candidates(int workload, int64_t n)
     for (int t : tiles)
         for (int m : maps) {
             c.push_back({t, m, 0u});
-            if (m == TRI_MAP_LAMBDA) {
+            if (m == TRI_MAP_LAMBDA && order_acts(workload, t, ld)) {
                 c.push_back({t, m, (uint32_t)TRI_FLAG_XCD_SWIZZLE});
                 c.push_back({t, m, (uint32_t)TRI_FLAG_ORDER_REVERSE});
                 c.push_back({t, m, (uint32_t)TRI_FLAG_ORDER_PAIRS});
@@ -142,32 +156,32 @@ static std::vector<Candidate> candidates(int workload, int64_t n)
             c.push_back({128, TRI_MAP_LAMBDA, (uint32_t)TRI_FLAG_STRIP_COLS | TRI_FLAG_XCD_SWIZZLE | st});
             c.push_back({128, TRI_MAP_LAMBDA, (uint32_t)TRI_FLAG_STRIP_COLS | TRI_FLAG_EDM_PIPE | st});
         }
-    if (workload == TRI_TUNE_LIFE)  // tile 64 in strips of 4 and 8 tiles, both forms
+    if (workload == TRI_TUNE_LIFE)  // tile 64 in strips of 4 and 8 tiles
         for (uint32_t st : {(uint32_t)TRI_FLAG_STRIP(2), (uint32_t)TRI_FLAG_STRIP(3)}) {
+            c.push_back({64, TRI_MAP_LAMBDA, st});
+            c.push_back({64, TRI_MAP_LAMBDA, st | (uint32_t)TRI_FLAG_STRIP_ALIGN});
+            c.push_back({64, TRI_MAP_LAMBDA, st | (uint32_t)TRI_FLAG_XCD_SWIZZLE});
+            // neighbouring tiles moved in pairs
+            const uint32_t w = (uint32_t)TRI_FLAG_LIFE_WIDE;
+            c.push_back({64, TRI_MAP_LAMBDA, st | w | (uint32_t)(TRI_FLAG_STRIP_ALIGN | TRI_FLAG_XCD_SWIZZLE)});
+            c.push_back({64, TRI_MAP_LAMBDA, st | w | (uint32_t)(TRI_FLAG_STRIP_ALIGN | TRI_FLAG_XCD_SWIZZLE |
+                                                              TRI_FLAG_ORDER_PAIRS)});
+            // (several generations a launch: BB's strips alone, lambda takes
+            // windows of its own whatever these flags)
             for (uint32_t tf : {0u, (uint32_t)TRI_FLAG_LIFE_TEMPORAL}) {
                 c.push_back({64, TRI_MAP_BB, st | tf});
-                c.push_back({64, TRI_MAP_LAMBDA, st | tf});
-                c.push_back({64, TRI_MAP_LAMBDA, st | tf | (uint32_t)TRI_FLAG_STRIP_ALIGN});
-                c.push_back({64, TRI_MAP_LAMBDA, st | tf | (uint32_t)TRI_FLAG_XCD_SWIZZLE});
-            }
-            // neighbouring tiles moved in pairs, both forms
-            const uint32_t w = (uint32_t)TRI_FLAG_LIFE_WIDE;
-            for (uint32_t tf : {0u, (uint32_t)TRI_FLAG_LIFE_TEMPORAL}) {
                 c.push_back({64, TRI_MAP_BB, st | w | tf});
-                c.push_back({64, TRI_MAP_LAMBDA, st | w | tf | (uint32_t)(TRI_FLAG_STRIP_ALIGN | TRI_FLAG_XCD_SWIZZLE)});
-                c.push_back({64, TRI_MAP_LAMBDA, st | w | tf | (uint32_t)(TRI_FLAG_STRIP_ALIGN | TRI_FLAG_XCD_SWIZZLE |
-                                                                       TRI_FLAG_ORDER_PAIRS)});
             }
         }
     if (workload == TRI_TUNE_LIFE)  // temporal blocking (tiles 16..64)
         for (int t : {16, 32, 64}) {
             c.push_back({t, TRI_MAP_BB, (uint32_t)TRI_FLAG_LIFE_TEMPORAL});
             c.push_back({t, TRI_MAP_LAMBDA, (uint32_t)TRI_FLAG_LIFE_TEMPORAL});
+            if (t == 64) continue;  // (windows, as above)
             c.push_back({t, TRI_MAP_LAMBDA, (uint32_t)(TRI_FLAG_LIFE_TEMPORAL | TRI_FLAG_XCD_SWIZZLE)});
             c.push_back({t, TRI_MAP_LAMBDA, (uint32_t)(TRI_FLAG_LIFE_TEMPORAL | TRI_FLAG_XCD_SWIZZLE |
                                                        TRI_FLAG_ORDER_PAIRS)});
         }
-    (void)n;
     return c;
 }
 
@@ -286,7 +300,7 @@ tri_status tri_autotune(int workload, int64_t n, int64_t d, int reps, int use_ca
     tri_tune_choice bestc{0, -1, 0u, 0.f};
     int32_t nall = 0;
     st = TRI_OK;
-    for (const Candidate &cd : candidates(workload, n)) {
+    for (const Candidate &cd : candidates(workload, ld)) {
         tri_plan *p = nullptr;
         if (tri_map_plan(&p, n, cd.tile, cd.map, edm ? 0 : 1, cd.flags) != TRI_OK) continue;
         auto run = [&]() -> tri_status {

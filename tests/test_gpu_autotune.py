@@ -85,3 +85,27 @@ def _check_choice(tm, workload, n, d, ch):
         nz = e > 0
         rel = np.abs(got.astype(np.float64)[nz] - e[nz]) / e[nz]
         assert rel.max() <= ((d + 2) * U / 2 + U if mode == tm.EDM_FP32 else 1e-3)
+
+
+@pytest.mark.parametrize("workload,n,d", [(0, 1000, 0), (0, 1024, 0), (1, 1000, 0), (1, 1024, 0),
+                                          (2, 1000, 8), (3, 300, 32), (3, 300, 8)])
+def test_autotune_times_no_launch_twice(workload, n, d):
+    """Flags that a kernel ignores make no candidates of their own."""
+    tm = _tm()
+    tm.tune_cache_clear()
+    note("autotune candidates", workload, n, d)
+    _, allc = tm.autotune(workload, n, d, reps=1, use_cache=False)
+    assert len({(c["tile"], c["map"], c["flags"]) for c in allc}) == len(allc)
+    orders = tm.FLAG_XCD_SWIZZLE | tm.FLAG_ORDER_REVERSE | tm.FLAG_ORDER_PAIRS
+    for tile in {c["tile"] for c in allc}:
+        lam = [c["flags"] for c in allc if c["tile"] == tile and c["map"] == "lambda"]
+        if workload == 2:
+            temporal = [f for f in lam if f & tm.FLAG_LIFE_TEMPORAL]
+            assert len(temporal) == {8: 0, 16: 3, 32: 3, 64: 1}[tile]
+        elif workload == 3:
+            assert lam == [0]
+        else:
+            plain = [f for f in lam if f & ~orders == 0]
+            swizzled = n % 32 != 0 and (workload == 0 or tile < 32)
+            assert len(plain) == (1 if swizzled else 5), tile
+    tm.tune_cache_clear()
