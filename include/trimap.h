@@ -50,7 +50,12 @@ typedef enum {
     TRI_MAP_LAMBDA = 4  /* lambda(omega): exactly m(m+1)/2 blocks (Eq. eq_gmap) */
 } tri_map;
 
-/* Plan flags (bit set). */
+/* Plan flags (bit set).  The orders (swizzle, reverse, pairs) set in which
+ * order lambda's workgroups visit omega and change no result.  Kernels that need
+ * an order of their own ignore them: the FP32 distance map, the fp32 elementwise
+ * body and int32 / four-feature tiles below 32 whose rows do not all start on
+ * 128-byte lines (swizzled: the halves of a line that two tiles write meet in
+ * one L2), and Life windows of several generations (see tri_launch_stencil). */
 enum {
     TRI_FLAG_XCD_SWIZZLE = 1u, /* lambda: give each XCD a contiguous range of omega   */
     TRI_FLAG_SQRT_RSQ = 2u,    /* lambda: sqrt(x) as x * rsq(x) (the paper's lambda_R) */
@@ -69,7 +74,8 @@ enum {
 /* Plan flags, bits 8..11: the number of consecutive tiles of the map that one
  * workgroup walks in the kernels that take strips (the distance map's MFMA
  * modes, the fp32 elementwise kernel at tiles 16 and 32 with 16-byte rows,
- * the bit-sliced Life kernel at tile 64 with 16-byte rows):
+ * the bit-sliced Life kernel at tile 64 with 16-byte rows, but for lambda's
+ * windows of several generations):
  * TRI_FLAG_STRIP(k) asks for G = 2^k tiles (k = 0..5, G = 1..32); none of
  * these bits set: G chosen from the tile count in the distance map, one
  * tile per workgroup elsewhere.  Kernels without strips ignore them. */
@@ -99,9 +105,9 @@ enum {
  * T_{2p+r} + c).  TRI_FLAG_STRIP_COLS and TRI_FLAG_STRIP_ALIGN take
  * precedence.  The distance map and the stencil reject it. */
 #define TRI_FLAG_STRIP_BAND 0x8000u
-/* Plan flag for the bit-sliced Life strips (tile 64, 16-byte rows), in
- * both forms (one generation with the paper's 1-cell halo, and with
- * TRI_FLAG_LIFE_TEMPORAL up to 16 generations with a 16-cell halo): a wave
+/* Plan flag for the bit-sliced Life strips (tile 64, 16-byte rows), one
+ * generation a launch with the paper's 1-cell halo, or, under BB, RB and REC,
+ * with TRI_FLAG_LIFE_TEMPORAL up to 16 generations with a 16-cell halo: a wave
  * moves tiles 2 j and 2 j + 1 of its strip as one window two tiles wide
  * when they are neighbours in a tile row (every row segment a whole
  * 128-byte line; the temporal window's halo shares the edge words with the
@@ -263,7 +269,8 @@ tri_status tri_tet_dummy(const tri_tet *plan, int32_t target, int32_t *sink, voi
  * With TRI_FLAG_LIFE_TEMPORAL in the plan (tiles 16, 32, 64; no graph) one
  * launch advances several generations: under lambda at tile 64 (ld >= 16) up
  * to 32 (50 up to n = 1536), in windows of the domain that the library tiles
- * for the launch and lambda numbers; else up to four from a tile staged with
+ * for the launch and lambda numbers, whatever strips, pairs of tiles or order
+ * the plan's flags ask for; else up to four from a tile staged with
  * a 4-cell halo (up to sixteen with a 16-cell halo for 64 x 64 tiles on grids of at
  * least 512 tiles whose ld is a multiple of 16 and whose buffers are
  * 16-byte aligned), the number of launches keeping the parity of `steps`.
@@ -380,8 +387,9 @@ typedef struct {
 
 /* Plan a batch from host arrays kind[count], n[count], d[count] (d ignored
  * for Life).  flags: 0 or TRI_FLAG_LIFE_TEMPORAL (life_tile >= 16: each node
- * advances the Life instances by up to four generations, as in
- * tri_launch_stencil; the number of nodes keeps the parity of life_steps).
+ * advances the Life instances by up to four generations, or up to 32 where
+ * tri_batch_bind takes windows; the number of nodes keeps the parity of
+ * life_steps).
  * Needs the device that will run it to be current: it queries the CU count
  * and occupancy and allocates the plan's own device arrays (prefix sums,
  * instance descriptors, counters).  n_k < 2^20; at most 2^31 tiles per
@@ -435,7 +443,8 @@ tri_status tri_batch_autotune(int32_t count, const int32_t *host_kind, const int
  * tri_autotune times every candidate (tiles 8/16/32/64 — plus 128 for the
  * fp32 elementwise body, 16/32/64/128 for the FP32 distance map, 128 for the
  * MFMA one — times maps BB, RB, REC (when
- * m is a power of two) and lambda, the latter plain, with
+ * m is a power of two) and lambda, the latter plain and, where the kernel
+ * takes the plan's order, with
  * TRI_FLAG_XCD_SWIZZLE, TRI_FLAG_ORDER_REVERSE, TRI_FLAG_ORDER_PAIRS and
  * swizzle + pairs, plus UTM for the elementwise bodies and Life) on this
  * GPU: one warm-up and `reps` timed calls, each between two HIP events on
@@ -446,8 +455,8 @@ tri_status tri_batch_autotune(int32_t count, const int32_t *host_kind, const int
  * pair).  d is the dimension of the distance maps; for Life it is the
  * number of generations of one timed call (0: 32), so that a caller ranks
  * the candidates on the schedule it runs.  Life candidates include
- * TRI_FLAG_LIFE_TEMPORAL for BB and lambda at tiles 16..64 (lambda plain,
- * swizzled, or swizzled in the pairs order); Life times are reported per
+ * TRI_FLAG_LIFE_TEMPORAL for BB and lambda at tiles 16..64 (lambda plain, and
+ * at tiles 16 and 32 swizzled or swizzled in the pairs order); Life times are reported per
  * generation.  The fastest candidate goes to *best and into a process-wide
  * cache keyed by GPU architecture, CU count, workload, floor(log2 n) and d
  * (distance maps and Life); with

@@ -1738,10 +1738,12 @@ static tri_status edm_run(const tri_plan *p, const float *x, int64_t d, int64_t 
     if (((uintptr_t)x | (uintptr_t)out) & 3) return fail(TRI_E_INVAL, "tri_edm: unaligned buffer");
     hipStream_t s = (hipStream_t)stream;
     if (mode == TRI_EDM_FP32) {
-        EdmArgs a{plan_tile_grid(p), EdmTile{(int32_t)p->n, (int32_t)d, ldx, x, out}};
+        // (neighbouring tiles on one XCD, whatever the plan's order: the parts of a
+        // line that they write meet in its L2)
+        const EdmArgs a{plan_tile_grid_swizzled(p),
+                        EdmTile{(int32_t)p->n, (int32_t)d, ldx, x, out}};
         // where the matrix cores are both nearer and faster (see edm_gram_body)
         const bool gram = edm_gram_takes(p->tile, d, ldx);
-        a.g = plan_tile_grid_swizzled(p);
         if (!(gram ? edm_gram(p, a, s) : edm_f32(p, a, s))) return fail(TRI_E_UNSUPPORTED, "tri_edm: tile");
         TRI_HIP(hipGetLastError());
         return TRI_OK;
