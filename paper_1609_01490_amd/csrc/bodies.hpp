@@ -13,7 +13,8 @@ namespace trimap {
 // ---------------------------------------------------------------------------
 // Correctly rounded square root in five operations for x in [2^-96, 2^96]:
 // one Newton step from x rsq(x).  It equals the correctly rounded root for
-// every binary32 value of that range (all of them compared on the device);
+// every binary32 value of that range (all of them compared on the device; the
+// tests compare those of six binades, of both parities and at both ends);
 // __builtin_sqrtf, right for every x, takes about sixteen.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float sqrt_near1(float x)

@@ -142,3 +142,34 @@ def test_edm4_full_size_whole_triangle():
     print(f"[edm4 whole triangle] {len(res)} bands checked", flush=True)
     assert sum(r[0] for r in res) == 0, [r[0] for r in res]
     assert sum(r[1] for r in res) == 0, [r[1] for r in res]
+
+
+@pytest.mark.parametrize("exponent", [0, 1, -96, -95, 94, 95])
+@pytest.mark.parametrize("ld", [6272, 6273])
+def test_edm4_root_of_every_float(exponent, ld):
+    """The short square root against the correctly rounded one for all 2^23
+    floats of a binade, of both parities and at both ends of its range
+    [2^-96, 2^96]: rows x with x^2 in steps of 2^-11, columns y with y^2 of 0 ..
+    4223 units in the last place, so that the sums of their squares are every
+    float of [2^exponent, 2^(exponent + 1))."""
+    import torch
+    tm = _tm()
+    f = np.float32
+    cols, rows = 4224, 2048
+    n = cols + rows
+    y = np.sqrt(2.0 ** exponent * np.arange(cols) * 2.0 ** -23).astype(f)
+    x = np.sqrt(2.0 ** exponent * (1 + np.arange(rows) * 2.0 ** -11)).astype(f)
+    low, high = f(2.0 ** exponent), f(2.0 ** (exponent + 1))
+    x = np.where(x * x < low, np.nextafter(x, f(np.inf)), x)
+    sq = ((x * x)[:, None] + (y * y)[None]).astype(f)
+    # (an odd power of two is no square of a float itself)
+    assert len(np.unique(sq[(sq >= low) & (sq < high)])) == 2 ** 23 - exponent % 2
+    P = np.zeros((n, 4), dtype=f)
+    P[:cols, 1] = y
+    P[cols:, 0] = x
+    note("edm4 roots", exponent, ld)
+    c = torch.zeros((n, ld), dtype=torch.float32, device="cuda")
+    tm.Plan(n, 64, "lambda").elementwise(tm.OP_EDM4_F32, dev(P), None, c)
+    got = host(c[cols:, :cols])
+    want = np.sqrt(sq)
+    assert (got.view(np.uint32) == want.view(np.uint32)).all(), int((got != want).sum())
