@@ -715,7 +715,9 @@ tri_status tri_batch_launch(tri_batch *b, int how, void *stream)
     case TRI_BATCH_STREAM:
         return batch_enqueue(b, s);
     case TRI_BATCH_PER_INSTANCE: {
-        // the same tile bodies, one launch per instance and generation
+        // one launch per instance and generation (temporal: schedule entry), with the
+        // same tile bodies but for Life windows, whose shape follows the grid's size
+        // and the generations there (same cells)
         for (int32_t k = 0; k < b->count; ++k) {
             const BatchDesc &D = b->desc[k];
             const int64_t ne = D.kind == TRI_KIND_EDM ? D.n - 1 : D.n;

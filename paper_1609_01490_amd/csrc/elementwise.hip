@@ -877,8 +877,9 @@ static bool dispatch_rows(const tri_plan *p, ElemArgs args, bool vector, bool li
         strip_flag_len(p->flags))
         return axpyt_strips(p, args, s);
     if (lines) {
-        // matrices that the L2s hold: cached accesses save a tenth (n = 2048,
-        // tile 32 4.9 -> 4.2 us, n = 4096 18.0 -> 16.3; n = 8192 77 -> 85)
+        // matrices whose triangles take half of the memory-side cache (256 MB) at
+        // most: cached accesses save a tenth (n = 2048, tile 32 4.9 -> 4.2 us, n =
+        // 4096 18.0 -> 16.3; n = 8192, 400 MB, 77 -> 85)
         if (OP == TRI_OP_AXPYT_F32 && p->elements * 12 <= (128ll << 20))
             return dispatch_map<OP, kVector>(p, args, s);
         // outputs beyond the memory-side cache (256 MB): see k_edm4
