@@ -35,6 +35,27 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
+TABLE_MAX = 8  # numbers that a table of the result line may hold
+
+
+def split_tables(res, path="", tables=None):
+    """`res` without its tables of more than TABLE_MAX numbers (timings of
+    every candidate), and those tables by their path: the one line of results
+    stays short enough to be kept whole, the tables go to the log."""
+    tables = {} if tables is None else tables
+    out = {}
+    for k, v in res.items():
+        name = f"{path}/{k}" if path else k
+        if isinstance(v, dict):
+            if len(v) > TABLE_MAX and all(isinstance(x, (int, float)) for x in v.values()):
+                tables[name] = v
+            else:
+                out[k] = split_tables(v, name, tables)[0]
+        else:
+            out[k] = v
+    return out, tables
+
+
 class Timer:
     """HIP events on the stream the kernels are launched on."""
 
@@ -518,7 +539,7 @@ def bench_edm(tm, torch, timer, check=True):
         res["accuracy_rows"] = (f"{len(rows)} whole rows: 4096 seeded random rows and the row "
                                 f"of every one of the {len(dup_pairs)} near-duplicate pairs; "
                                 f"FP64 oracle on {thr} host threads, {dt:.1f} s")
-    digest = src_digest("edm.hip", "maps.hpp")
+    digest = src_digest("edm.hip", "edm_gram.hpp", "bodies.hpp", "maps.hpp")
     for mode, name in ((tm.EDM_BF16X3, "bf16x3"), (tm.EDM_BF16, "bf16")):
         ws = torch.empty(q.edm_workspace_size(d, mode), dtype=torch.uint8, device="cuda")
         # the GPU idled during the host oracle above: warm up for longer,
@@ -861,7 +882,7 @@ def main():
     ms, tile, flags = res[args.map]
     bytes_per_launch = 12 * E
     achieved = bytes_per_launch / (ms * 1e-3) / 1e9
-    digest = src_digest("elementwise.hip", "maps.hpp")
+    digest = src_digest("elementwise.hip", "bodies.hpp", "maps.hpp")
     traffic = traffic_from_profiles(f"axpyt_f32_n{n}_{args.map}_t{tile}_f{flags}", digest)
 
     extra = {"stream_add_ceiling_GBps": round(res["stream_add_GBps"], 1),
@@ -889,6 +910,9 @@ def main():
             except Exception as e:  # keep the main line even if an extra fails
                 extra[name] = {"error": str(e)}
 
+    extra, tables = split_tables(extra)
+    for name, table in tables.items():
+        log("table", name, json.dumps(table))
     line = {
         "metric": "elements/s + HBM GB/s %peak, λ(ω) vs bounding-box; "
                   "EDM pairs/s BF16 vs FP32",
