@@ -829,6 +829,22 @@ def profile_target(tm, torch, args):
         nxt = torch.zeros_like(cur)
         p = tm.Plan(n, args.tile or 64, args.map, flags=args.flags)
         p.stencil(cur, nxt, reps)
+    elif t in ("collide", "collide_1d"):
+        n, dim = 131072, 1 if t == "collide_1d" else 3
+        sd = torch.from_numpy(inputs.spheres(n, dim)).cuda()
+        counts = torch.empty(n, dtype=torch.int32, device="cuda")
+        p = tm.Plan(n, args.tile or 128, args.map, include_diag=False, flags=args.flags)
+        for _ in range(reps):
+            p.collide(sd, counts, dim=dim)
+    elif t == "triangles":
+        n = 8192
+        P, r2 = inputs.points3(n)
+        pd = torch.from_numpy(P).cuda()
+        counts = torch.empty(n, dtype=torch.int32, device="cuda")
+        total = torch.empty(1, dtype=torch.int64, device="cuda")
+        q = tm.TetPlan(n, args.tile or 64, args.map)
+        for _ in range(reps):
+            q.triangles(pd, float(r2), counts, total)
     elif t == "batch":
         tiles = (args.tile, args.tile, args.flags) if args.tile else None
         spec, kinds, A, B, b, *_ = make_batch(tm, torch, tiles=tiles)
@@ -859,7 +875,8 @@ def main():
     ap.add_argument("--no-extra", action="store_true")
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--profile-target", choices=["elementwise", "edm", "edm_bf16", "edm_fp32", "life",
-                                                 "int", "copy", "batch"],
+                                                 "int", "copy", "batch", "collide", "collide_1d",
+                                                 "triangles"],
                     help="only launch this workload's kernels a few times (for rocprofv3 runs); "
                          "prints no JSON line")
     args = ap.parse_args()

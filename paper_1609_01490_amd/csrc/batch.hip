@@ -208,11 +208,12 @@ __global__ void __launch_bounds__(kBatchThreads, 4) k_batch_step(BatchStepArgs a
 // instance stages its coordinates as 16-byte vectors (chosen at bind time, so
 // that the kernel holds one distance body).
 //
-// Both halves are bound by vector issue.  512 instances, n log-uniform in [64,
-// 8192], half of them Life for 20 generations in two nodes: the second node 930
-// -> 630 us against windows of two 64 x 64 tiles per wave in LDS; 100 instances
-// up to n = 1024, 19 generations in one node instead of three, d = 3: 181 -> 54
-// us in all.
+// The vector units are the busiest in both halves (67 % of the cycles of the first
+// node, 52 % of the second, whose claims also wait for their loads and barriers).
+// 512 instances, n log-uniform in [64, 8192], half of them Life for 20 generations
+// in two nodes: the second node 930 -> 630 us against windows of two 64 x 64 tiles
+// per wave in LDS; 100 instances up to n = 1024, 19 generations in one node instead
+// of three, d = 3: 181 -> 54 us in all.
 struct BatchWindowArgs {
     const BatchDesc *desc;
     const int64_t *life, *edm;      // item prefixes of the Life and distance instances

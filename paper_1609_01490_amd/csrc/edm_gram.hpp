@@ -112,7 +112,8 @@ __device__ __forceinline__ void lds_barrier()
 // Work.  The direct form is bound by two vector operations per pair and
 // dimension.  Here they are about 5 per staged coordinate and 10 per pair, and
 // with the products (half as long, on the matrix cores, partly in their shadow)
-// and the power limit's clock they bound the kernel.  n = 16384: d = 128 706 ->
+// and the power limit's clock they bound the kernel (n = 65536, d = 128: the vector
+// units busy 72 % of the cycles, the matrix cores 25 %).  n = 16384: d = 128 706 ->
 // 234 us (tile 128) and 770 -> 288 us (tile 64), d = 64 404 -> 172 us; n = 10007,
 // d = 256 515 -> 143 us; n = 2000, d = 128 26.0 -> 11.4 us.  Below d = 64 against
 // the direct form as it is now, tile 64 / 128: n = 16384, d = 32 247 -> 172 /

@@ -199,7 +199,7 @@ __device__ __forceinline__ bool near3(f4 a, f4 b, float r2)
 // With the three relations of every tile formed anew (3 rho^2 distance tests
 // a tile, and a sweep over rho^2 pairs), n = 8192 under lambda took 1.50 ms at
 // tile 64 and 3.86 at tile 32; in this form 0.10 and 0.14.  What bounds it is
-// vector issue: 71 % of its cycles at 45 million wave instructions, about 16
+// vector issue: 61 % of its cycles at 39 million wave instructions, about 16
 // per edge and 64 points c and 14 per ballot of the a-b relation.
 constexpr int kTriThreads = 256;
 
