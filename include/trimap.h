@@ -295,12 +295,12 @@ tri_status tri_launch_stencil(const tri_plan *plan, uint8_t *cur, uint8_t *nxt, 
  *    ones, relative to them.  From 32 dimensions on, tiles of 64 and 128 take
  *    d^2 from FP32 norms about a centre of the tile and a split product on the
  *    matrix cores, within (5 d / 12 + 24) 2^-24; near pairs, pairs far smaller
- *    than their tile's spread and sums out of range are direct.  Measured on
- *    uniform, normal, log-normal and unit vectors the largest error is about
- *    the direct sum's at d = 32 and less from there on (uniform points d =
- *    128: 2.6e-7, direct 4.8e-7), and the root mean square is less throughout;
- *    on features that are mostly zeros the largest is up to twice the direct
- *    sum's below d = 96.  Whole multiples of a power of two whose norms about
+ *    than their tile's spread and sums out of range are direct.  Measured, the
+ *    root mean square error is no larger than the direct sum's, and the largest
+ *    is smaller on uniform, normal and unit vectors (uniform points, d = 128:
+ *    2.6e-7, direct 4.8e-7), up to a quarter larger below d = 64 on heavier tails
+ *    (log-normal, Laplace), and up to twice the direct sum's below d = 128 on
+ *    features that are mostly zeros.  Whole multiples of a power of two whose norms about
  *    the centre sum to less than 2^24 of its squares give the correctly rounded
  *    distances in both forms.
  *  - TRI_EDM_BF16X3 / TRI_EDM_BF16: plan tile 128; `out` 16-byte aligned

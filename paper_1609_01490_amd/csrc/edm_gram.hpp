@@ -71,8 +71,8 @@ __device__ __forceinline__ void lds_barrier()
 // v_mfma_f32_32x32x16_f16.
 //
 // Error.  Rounding leaves about 2^-24 (|y_i|^2 + |y_j|^2) in d^2, whatever d,
-// while the direct sum's error grows with d.  A pair with d^2 < kGramNear of
-// that sum, or with a sum that is no finite number well inside FP32's range, is
+// while the direct sum's error grows with d.  A pair with d^2 below 3/8 of
+// that sum (from 128 dimensions on 1/2), or with a sum that is no finite number well inside FP32's range, is
 // recomputed from the differences in the direct body's order.  So is a pair whose
 // sum is small in scaled units: a coordinate below 1/4 keeps 2^-25 in its halves
 // and no relative precision, which adds up to 2^-24 sqrt(2 d S) to d^2, S the sum
@@ -95,11 +95,15 @@ __device__ __forceinline__ void lds_barrier()
 // 4.0e-8 and 4.8e-7 / 2.6e-7 at d = 128, 1.3e-7 / 3.5e-8 and 6.4e-7 / 2.5e-7 at
 // d = 256; d = 128 in clusters of 0.6 times their centres' spread 9.1e-8 /
 // 4.0e-8 and 4.5e-7 / 3.7e-7.  Hence the line at 32: below it the largest error
-// would be larger than the direct sum's.  Normal, log-normal, Laplace and unit
-// vectors are like it.  Features that are mostly zeros are the exception, since few
-// terms of the direct sum round (a normal variable less 0.8, cut at zero, 8
-// million pairs, L2 and largest): d = 32 3.8e-8 / 3.8e-8 and 2.2e-7 / 3.9e-7, d =
-// 63 4.5e-8 / 3.7e-8 and 2.6e-7 / 3.5e-7, d = 96 5.3e-8 / 3.8e-8 and 3.2e-7 / 3.3e-7.
+// would be larger than the direct sum's.  Normal and unit vectors are like it.  On
+// log-normal, Laplace and half-normal ones the largest error of 8 million pairs
+// is up to a quarter larger than the direct sum's below d = 64 (4.6e-7 against
+// 3.8e-7, log-normal, d = 40), and on features that are mostly zeros, few of
+// whose terms round in the direct sum, it is larger up to d = 96 (a normal variable
+// less 0.8, cut at zero, L2 and largest): d = 32 3.8e-8 / 3.8e-8 and 2.2e-7 /
+// 3.9e-7, d = 63 4.5e-8 / 3.7e-8 and 2.6e-7 / 3.5e-7, d = 96 5.3e-8 / 3.8e-8 and
+// 3.2e-7 / 3.3e-7.  With the wider near line from 128 dimensions on it was larger on
+// none of these (tried at d = 128 and 200).
 //
 // A tile with many pairs to recompute is left to the direct body, most of the
 // time after 32 dimensions.  Where every tile is (ten tight clusters in random
@@ -132,7 +136,11 @@ __device__ __forceinline__ void lds_barrier()
 // 267 us).
 // ---------------------------------------------------------------------------
 constexpr int kGramMinDims = 32;
-constexpr float kGramNear = 0.375f;
+// The near line, of the norms' sum: 3/8, and from 128 dimensions on, where such pairs
+// are rare on ordinary data, 1/2, which costs nothing there (d = 128 223 -> 224 us, d
+// = 64 160 -> 176, d = 32 146 -> 169, the batch's d = 32 8 %).
+constexpr float kGramNear = 0.375f, kGramNearWide = 0.5f;
+constexpr int kGramWideDims = 128;
 constexpr float kGramFloor = 8.f;  // per dimension, on d^2 in scaled units
 constexpr int kGramK = 16;         // dimensions per staged chunk
 constexpr int kGramLaneNear = 4;   // near pairs per lane (of 32 or 16) that a tile may hold
@@ -371,6 +379,7 @@ __device__ __forceinline__ void edm_gram_body(const EdmTile &p, int32_t bi, int3
     // 2^30 are finite) makes its pairs' sums NaN, and those pairs near
     const float mi = norm(ni), mj = norm(nj);
     const float inv2 = 1.f / (sc * sc);
+    const float line = d >= kGramWideDims ? kGramNearWide : kGramNear;
     const float least = fmaxf(0x1p-90f, kGramFloor * (float)d * inv2);
     if (kq == 0) {
         sN[pt] = mi < 0x1p30f && mi * inv2 < 0x1p93f ? mi * inv2 : __builtin_nanf("");
@@ -391,7 +400,7 @@ __device__ __forceinline__ void edm_gram_body(const EdmTile &p, int32_t bi, int3
                 const float s = si[u] + sj;
                 const float v = __builtin_fmaf(-2.f * inv2, acc[a][4 * q + u], s);
                 acc[a][4 * q + u] = v;
-                near |= !(v >= __builtin_fmaf(s, kGramNear, least));
+                near |= !(v >= __builtin_fmaf(s, line, least));
             }
         }
     uint32_t m = 0;                        // this lane's near pairs: bit 16 a + r
@@ -404,7 +413,7 @@ __device__ __forceinline__ void edm_gram_body(const EdmTile &p, int32_t bi, int3
             for (int r = 0; r < 16; ++r) {
                 const int dr = 32 * a + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
                 const float s = sN[o + WT * wr + dr] + sj;
-                if (!(acc[a][r] >= __builtin_fmaf(s, kGramNear, least)) && j < R0 + dr &&
+                if (!(acc[a][r] >= __builtin_fmaf(s, line, least)) && j < R0 + dr &&
                     R0 + dr < n)
                     m |= 1u << (16 * a + r);
             }
