@@ -337,8 +337,7 @@ __global__ void __launch_bounds__(kCollideThreads, 4) k_collide_gram(CollideArgs
                                                              __float_as_uint(g[a][r + 1]), 0xfe);
                     any |= neg[a];
                 }
-                const uint64_t passed = __ballot((int32_t)any < 0);
-                if (passed == 0) continue;
+                if (!__any((int32_t)any < 0)) continue;
                 // rare: the exact test of the pairs that passed, each lane its own
                 const int32_t j = cb + 32 * b + (l & 31);
                 const bool live = j < c1;
@@ -363,7 +362,7 @@ __global__ void __launch_bounds__(kCollideThreads, 4) k_collide_gram(CollideArgs
                 // exact test of every pair takes 280.  From 16 lanes on, blocks with
                 // a few overlaps took it too: n = 300 to 5000, four per sphere 7.7 ->
                 // 8.1 us; n = 9300, 194 per sphere 74 -> 25.)
-                if (__builtin_expect(__builtin_popcountll(passed) > 56, 0)) {
+                if (__builtin_expect(__builtin_popcountll(__ballot(m != 0)) > 56, 0)) {
                     for (int q = l; q < TILE; q += 64) hits[w][q] = 0;
                     __builtin_amdgcn_wave_barrier();
                     int32_t mine = 0;
