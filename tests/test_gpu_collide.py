@@ -103,6 +103,23 @@ def test_collide_filters_miss_nothing(tile, kind):
                 assert (host(counts) == exp).all(), (kind, tile, map_name, n, dim)
 
 
+@pytest.mark.parametrize("kind", ["tiny", "small", "huge", "offset", "outliers", "sorted", "flat",
+                                  "big radii", "negative", "not finite"])
+def test_collide_filters_miss_nothing_at_tile_32(kind):
+    """The smallest sizes that take the filters at tile 32."""
+    import torch
+    tm = _tm()
+    for n in (7424, 7425):
+        for dim in (1, 3):
+            S = _spheres_of(kind, n, dim, np.random.default_rng(n + dim))
+            exp = oracle.collide(S, dim)
+            for map_name in ("lambda", "bb", "rb"):
+                note("collide tile 32", kind, map_name, n, dim)
+                counts = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+                tm.Plan(n, 32, map_name, include_diag=False).collide(dev(S), counts, dim=dim)
+                assert (host(counts) == exp).all(), (kind, map_name, n, dim)
+
+
 @pytest.mark.parametrize("map_name,even", [("lambda", True), ("bb", False), ("rb", True),
                                            ("rb", False), ("rec", True)])
 @pytest.mark.parametrize("tile", [32, 64, 128])
