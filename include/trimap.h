@@ -296,13 +296,14 @@ tri_status tri_launch_stencil(const tri_plan *plan, uint8_t *cur, uint8_t *nxt, 
  *    d^2 from FP32 norms about a centre of the tile and a split product on the
  *    matrix cores, within (5 d / 12 + 24) 2^-24; near pairs, pairs far smaller
  *    than their tile's spread and sums out of range are direct.  Measured, the
- *    root mean square error is no larger than the direct sum's, and the largest
- *    is smaller on uniform, normal and unit vectors (uniform points, d = 128:
- *    2.6e-7, direct 4.8e-7), up to a quarter larger below d = 64 on heavier tails
- *    (log-normal, Laplace), and up to twice the direct sum's below d = 128 on
- *    features that are mostly zeros.  Whole multiples of a power of two whose norms about
- *    the centre sum to less than 2^24 of its squares give the correctly rounded
- *    distances in both forms.
+ *    root mean square error is smaller than the direct sum's, and the largest
+ *    too on uniform and normal points (uniform points, d = 128: 2.6e-7, direct
+ *    4.8e-7).  The largest is up to 6 % larger at d = 32 and 40 on unit vectors, up
+ *    to a quarter larger below d = 64 on heavier tails (log-normal, Laplace), and
+ *    up to twice the direct sum's below d = 128 on features that are mostly zeros,
+ *    whose root mean square error is up to 3 % larger.  Whole multiples of a power
+ *    of two whose norms about the centre sum to less than 2^24 of its squares give
+ *    the correctly rounded distances in both forms.
  *  - TRI_EDM_BF16X3 / TRI_EDM_BF16: plan tile 128; `out` 16-byte aligned
  *    (rows are written as 16-byte vectors); ws a device buffer of at least
  *    tri_edm_workspace_size() bytes, 256-byte aligned, else TRI_E_NOMEM /

@@ -95,15 +95,17 @@ __device__ __forceinline__ void lds_barrier()
 // 4.0e-8 and 4.8e-7 / 2.6e-7 at d = 128, 1.3e-7 / 3.5e-8 and 6.4e-7 / 2.5e-7 at
 // d = 256; d = 128 in clusters of 0.6 times their centres' spread 9.1e-8 /
 // 4.0e-8 and 4.5e-7 / 3.7e-7.  Hence the line at 32: below it the largest error
-// would be larger than the direct sum's.  Normal and unit vectors are like it.  On
-// log-normal, Laplace and half-normal ones the largest error of 8 million pairs
+// would be larger than the direct sum's.  Normal points are like it; unit vectors'
+// and fourth powers' largest error is up to 6 % above it at d = 32 and 40.  On log-normal, Laplace and half-normal ones the largest error of 8 million pairs
 // is up to a quarter larger than the direct sum's below d = 64 (4.6e-7 against
 // 3.8e-7, log-normal, d = 40), and on features that are mostly zeros, few of
-// whose terms round in the direct sum, it is larger up to d = 96 (a normal variable
+// whose terms round in the direct sum, it is larger up to d = 127 (a normal variable
 // less 0.8, cut at zero, L2 and largest): d = 32 3.8e-8 / 3.8e-8 and 2.2e-7 /
-// 3.9e-7, d = 63 4.5e-8 / 3.7e-8 and 2.6e-7 / 3.5e-7, d = 96 5.3e-8 / 3.8e-8 and
-// 3.2e-7 / 3.3e-7.  With the wider near line from 128 dimensions on it was larger on
-// none of these (tried at d = 128 and 200).
+// 3.9e-7, d = 40, the worst found, 4.0e-8 / 3.8e-8 and 2.2e-7 / 4.1e-7, d = 63 4.5e-8 /
+// 3.7e-8 and 2.6e-7 / 3.5e-7, d = 96 5.3e-8 / 3.8e-8 and 3.1e-7 / 3.3e-7; less 1.5, d =
+// 50 3.3e-8 / 3.4e-8 and 1.9e-7 / 3.5e-7, d = 127 4.1e-8 / 3.9e-8 and 2.4e-7 / 3.3e-7.
+// With the wider near line from 128 dimensions on neither was larger on any of these
+// (tried at d = 128, 200, 256 and 400).
 //
 // A tile with many pairs to recompute is left to the direct body, most of the
 // time after 32 dimensions.  Where every tile is (ten tight clusters in random
